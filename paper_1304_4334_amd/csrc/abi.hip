@@ -110,6 +110,18 @@ int64_t chunk_capacity(const smc_model *m, const smc_particles *pop) {
   return std::min<int64_t>(kMaxChunk, (int64_t)((pop->ws_bytes - L.wcols) / (P * sizeof(double))));
 }
 
+// The test functions' values at date t, [G][P]: the particles' own rows for
+// the parameters, else computed into the workspace's gather area (G <= 2d + S
+// + 2 rows).
+smc_status test_rows(const smc_model *m, const smc_particles *pop, int64_t t, int32_t which,
+                     const double **rows, hipStream_t s) {
+  *rows = pop->theta;
+  if (which == SMC_TEST_PARAMS) return SMC_OK;
+  double *g = ws_at<double>(pop, ws_layout(m->dev, pop->J, pop->N).gather);
+  *rows = g;
+  return launch_test_fns(m->dev, (int64_t)pop->J * pop->N, pop->theta, pop->state, t, which, g, s);
+}
+
 int32_t state_bytes(const smc_model *m) { return m->dev.prec == SMC_FP32 ? 4 : 8; }
 
 // Page-locked, coherent host slot where the C-phase decision kernel stores
@@ -747,11 +759,10 @@ smc_status smc_test_moments(const smc_model *m, smc_particles *pop, int64_t t, i
   const int32_t G = smc_num_test_functions(m, which);
   if (G < 1) return set_error(SMC_E_INVALID_ARG, "test functions %d", which);
   hipStream_t s = as_stream(stream);
-  const int64_t P = (int64_t)pop->J * pop->N;
   const WsLayout L = ws_layout(m->dev, pop->J, pop->N);
-  double *g = ws_at<double>(pop, L.gather);  // [G][P], G <= 2d + S + 2 rows
-  if ((st = launch_test_fns(m->dev, P, pop->theta, pop->state, t, which, g, s))) return st;
-  return launch_report(g, pop->J, pop->N, G, ws_at<double>(pop, L.rpart), out, nullptr, s);
+  const double *rows = nullptr;
+  if ((st = test_rows(m, pop, t, which, &rows, s))) return st;
+  return launch_report(rows, pop->J, pop->N, G, ws_at<double>(pop, L.rpart), out, nullptr, s);
 }
 
 smc_status smc_log_score(int32_t L, int32_t J, const double *group_logwbar, const int64_t *t_end,
@@ -977,11 +988,10 @@ smc_status smc_run(const smc_model *m, smc_particles *pop, const smc_run_config 
         // mean RNE of the test functions; the higher threshold E2 after a C
         // phase that ended at a date of interest (Section 3.3)
         double *rne_d = ws_at<double>(pop, L.small + kSmallRne);
-        double *g = ws_at<double>(pop, L.gather);
-        double *rep = ws_at<double>(pop, L.small + kSmallCov);  // [G][4] scratch
-        if ((st = launch_test_fns(m->dev, P, pop->theta, pop->state, t_new, cfg->test_fn, g, s)) ||
-            (st = launch_report(g, pop->J, pop->N, G, ws_at<double>(pop, L.rpart), rep, rne_d,
-                                s)))
+        const double *rows = nullptr;
+        if ((st = test_rows(m, pop, t_new, cfg->test_fn, &rows, s)) ||
+            (st = launch_report(rows, pop->J, pop->N, G, ws_at<double>(pop, L.rpart), nullptr,
+                                rne_d, s)))
           return st;
         double rne = 0.0;
         if (hipMemcpyAsync(&rne, rne_d, sizeof(double), hipMemcpyDeviceToHost, s) != hipSuccess ||

@@ -1061,117 +1061,209 @@ __global__ void k_adapt(const int64_t *n_accept, int64_t P, int32_t target_permi
   *mh = v < 1 ? 1 : (v > 10 ? 10 : v);
 }
 
-// Per group j and parameter i: the group mean and the within-group sum of
-// squared deviations.
+// Group mean and within-group sum of squared deviations of function (or
+// parameter) i in group j: block (j, i), so that every column is read by a
+// block of its own.  Groups of up to kGroupRegs * kBlock particles are read
+// once and held in registers between the two sums.  (Bound by latency: one
+// load round trip and two block reductions.  One block per group looping over
+// the functions took 5 to 13 us at 64 groups of 1,024 and 2 to 5 functions.)
+constexpr int kGroupRegs = 8;
 __global__ void __launch_bounds__(256) k_rne_group(const double *theta, int64_t P, int32_t N,
-                                                   int32_t d, double *part) {
+                                                   double *part) {
   __shared__ double sh[4];
-  const int j = blockIdx.x;
-  for (int i = 0; i < d; ++i) {
-    const double *x = theta + i * P + (int64_t)j * N;
-    double s = 0.0;
+  const int j = blockIdx.x, i = blockIdx.y;
+  const double *x = theta + i * P + (int64_t)j * N;
+  const bool held = N <= kGroupRegs * kBlock;
+  double v[kGroupRegs];
+  double s = 0.0;
+  if (held) {
+#pragma unroll
+    for (int u = 0; u < kGroupRegs; ++u) {
+      const int n = threadIdx.x + u * kBlock;
+      v[u] = n < N ? x[n] : 0.0;
+    }
+#pragma unroll
+    for (int u = 0; u < kGroupRegs; ++u) s += v[u];
+  } else {
     for (int n = threadIdx.x; n < N; n += kBlock) s += x[n];
-    const double mean = block_reduce<OpSum<double>>(s, sh) / (double)N;
-    double q = 0.0;
+  }
+  const double mean = block_reduce<OpSum<double>>(s, sh) / (double)N;
+  double q = 0.0;
+  if (held) {
+#pragma unroll
+    for (int u = 0; u < kGroupRegs; ++u) {
+      const double e = v[u] - mean;
+      if (threadIdx.x + u * kBlock < N) q = fma(e, e, q);
+    }
+  } else {
     for (int n = threadIdx.x; n < N; n += kBlock) {
       const double e = x[n] - mean;
       q = fma(e, e, q);
     }
-    q = block_reduce<OpSum<double>>(q, sh);
-    if (threadIdx.x == 0) {
-      part[(int64_t)j * 2 * kDMax + i] = mean;
-      part[(int64_t)j * 2 * kDMax + kDMax + i] = q;
-    }
   }
-}
-
-// RNE_i = var-hat / v-hat with var-hat = (within SS + N sum_j (gbar_j - gbar)^2)
-// / (NJ - 1) and v-hat = N / (J - 1) sum_j (gbar_j - gbar)^2; mean over i.
-__global__ void k_rne_final(const double *part, int32_t J, int32_t N, int32_t d, double *rne) {
-  if (threadIdx.x != 0) return;
-  double acc = 0.0;
-  for (int i = 0; i < d; ++i) {
-    double g = 0.0, w = 0.0;
-    for (int j = 0; j < J; ++j) {
-      g += part[(int64_t)j * 2 * kDMax + i];
-      w += part[(int64_t)j * 2 * kDMax + kDMax + i];
-    }
-    g /= (double)J;
-    double b = 0.0;
-    for (int j = 0; j < J; ++j) {
-      const double e = part[(int64_t)j * 2 * kDMax + i] - g;
-      b += e * e;
-    }
-    const double var = (w + (double)N * b) / ((double)N * J - 1.0);
-    const double vhat = (double)N * b / (double)(J - 1);
-    acc += var / vhat;
+  q = block_reduce<OpSum<double>>(q, sh);
+  if (threadIdx.x == 0) {
+    part[(int64_t)j * 2 * kDMax + i] = mean;
+    part[(int64_t)j * 2 * kDMax + kDMax + i] = q;
   }
-  *rne = acc / (double)d;
 }
 
 // Moment report from k_rne_group's group means and within-group sums of
 // squares (Section 2.3): mean, sd = var-hat^(1/2), NSE (eq NSE_def), RNE =
-// var-hat / v-hat (eq vhat); and the mean RNE over the G functions.
-__global__ void k_report_final(const double *part, int32_t J, int32_t N, int32_t G, double *out,
-                               double *rne_mean) {
-  if (threadIdx.x != 0) return;
-  double acc = 0.0;
-  for (int i = 0; i < G; ++i) {
-    double g = 0.0, w = 0.0;
-    for (int j = 0; j < J; ++j) {
-      g += part[(int64_t)j * 2 * kDMax + i];
-      w += part[(int64_t)j * 2 * kDMax + kDMax + i];
+// var-hat / v-hat (eq vhat) with var-hat = (within SS + N sum_j (gbar_j -
+// gbar)^2) / (NJ - 1) and v-hat = N / (J - 1) sum_j (gbar_j - gbar)^2, to out
+// when given; and the mean RNE over the G functions.  The block loads 64
+// groups at a time into LDS, all columns together; thread i then adds those
+// of function i in group order.  (One thread reading every value from memory
+// in turn took 28 to 65 us at 64 groups.)
+constexpr int kReportTile = 64;  // groups per tile
+__global__ void __launch_bounds__(1024) k_report_final(const double *part, int32_t J, int32_t N,
+                                                       int32_t G, double *out,
+                                                       double *rne_mean) {
+  __shared__ double tg[kReportTile][kDMax + 1], tw[kReportTile][kDMax + 1], r[kDMax];
+  const int i = threadIdx.x;
+  auto load = [&](int32_t j0) {
+    __syncthreads();  // the tile before has been used
+    for (int e = threadIdx.x; e < kReportTile * kDMax; e += 1024) {
+      const int j = e / kDMax, c = e % kDMax;
+      if (j0 + j < J && c < G) {
+        tg[j][c] = part[(int64_t)(j0 + j) * 2 * kDMax + c];
+        tw[j][c] = part[(int64_t)(j0 + j) * 2 * kDMax + kDMax + c];
+      }
     }
-    g /= (double)J;
-    double b = 0.0;
-    for (int j = 0; j < J; ++j) {
-      const double e = part[(int64_t)j * 2 * kDMax + i] - g;
-      b += e * e;
+    __syncthreads();
+  };
+  double g = 0.0, w = 0.0, b = 0.0;
+  for (int32_t j0 = 0; j0 < J; j0 += kReportTile) {
+    load(j0);
+    if (i < G) {
+      const int n = min(kReportTile, J - j0);
+#pragma unroll 8
+      for (int j = 0; j < n; ++j) {
+        g += tg[j][i];
+        w += tw[j][i];
+      }
     }
+  }
+  g /= (double)J;
+  for (int32_t j0 = 0; j0 < J; j0 += kReportTile) {
+    if (J > kReportTile) load(j0);
+    if (i < G) {
+      const int n = min(kReportTile, J - j0);
+#pragma unroll 8
+      for (int j = 0; j < n; ++j) {
+        const double e = tg[j][i] - g;
+        b += e * e;
+      }
+    }
+  }
+  if (i < G) {
     const double var = (w + (double)N * b) / ((double)N * J - 1.0);
     const double vhat = (double)N * b / (double)(J - 1);
-    out[i * 4 + 0] = g;
-    out[i * 4 + 1] = sqrt(var);
-    out[i * 4 + 2] = sqrt(b / ((double)J * (J - 1)));
-    out[i * 4 + 3] = var / vhat;
-    acc += var / vhat;
+    if (out) {
+      out[i * 4 + 0] = g;
+      out[i * 4 + 1] = sqrt(var);
+      out[i * 4 + 2] = sqrt(b / ((double)J * (J - 1)));
+      out[i * 4 + 3] = var / vhat;
+    }
+    r[i] = var / vhat;
   }
-  if (rne_mean) *rne_mean = acc / (double)G;
+  if (!rne_mean) return;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double acc = 0.0;
+    for (int k = 0; k < G; ++k) acc += r[k];
+    *rne_mean = acc / (double)G;
+  }
 }
 
 // log wbar, its delta-method NSE and log wtilde from group_logwbar[L][J].
+// Rows (cycles) come through LDS in tiles, all loads of a tile in flight
+// together and its exponentials spread over the block; the sums run in the
+// order of the cycles and groups, one thread per group and per cycle.  (Each
+// thread reading its groups and cycles from memory took 28 us at 50 cycles of
+// 64 groups.)  Rows longer than a tile are read from memory in place.
+constexpr int kMlTile = 4096;   // doubles per tile
+constexpr int kMlGroups = 2047;  // longest row held in LDS
 __global__ void __launch_bounds__(256) k_log_ml(int32_t L, int32_t J, const double *g,
                                                 double *out) {
-  __shared__ double sh[4];
+  __shared__ double sh[4], tile[kMlTile], lwj[kMlGroups + 1];
   const int tid = threadIdx.x;
-  // log wbar_j = sum_l log wbar_j(l): each thread owns groups j = tid + 256 k
-  // and sums over the cycles in order.
-  auto lw = [&](int j) {
-    double s = 0.0;
-    for (int l = 0; l < L; ++l) s += g[(int64_t)l * J + j];
-    return s;
-  };
-  double m = -INFINITY;
-  for (int j = tid; j < J; j += kBlock) m = fmax(m, lw(j));
-  const double mx = block_reduce<OpMax<double>>(m, sh);
-  double r = 0.0;
-  for (int j = tid; j < J; j += kBlock) r += exp(lw(j) - mx);
-  const double rbar = block_reduce<OpSum<double>>(r, sh) / (double)J;
-  double q = 0.0;
-  for (int j = tid; j < J; j += kBlock) {
-    const double e = exp(lw(j) - mx) - rbar;
-    q = fma(e, e, q);
-  }
-  const double ss = block_reduce<OpSum<double>>(q, sh);
-  // log wtilde = sum_l log mean_j wbar_j(l): each thread owns cycles.
-  double lt = 0.0;
-  for (int l = tid; l < L; l += kBlock) {
-    const double *gl = g + (int64_t)l * J;
-    double ml = -INFINITY;
-    for (int j = 0; j < J; ++j) ml = fmax(ml, gl[j]);
-    double sl = 0.0;
-    for (int j = 0; j < J; ++j) sl += exp(gl[j] - ml);
-    lt += (ml > -INFINITY) ? ml + log(sl / (double)J) : -INFINITY;
+  double mx, rbar, ss, lt = 0.0;
+  if (J <= kMlGroups) {
+    const int pitch = J | 1;  // odd: neighbouring rows in different banks
+    const int nl = min(kBlock, kMlTile / pitch);  // rows per tile
+    for (int j = tid; j < J; j += kBlock) lwj[j] = 0.0;
+    for (int32_t l0 = 0; l0 < L; l0 += nl) {
+      const int n = min(nl, L - l0);
+      __syncthreads();  // the tile before has been used
+      for (int e = tid; e < n * J; e += kBlock)
+        tile[(e / J) * pitch + e % J] = g[(int64_t)l0 * J + e];
+      __syncthreads();
+      // log wbar_j = sum_l log wbar_j(l): thread j adds its group's cycles
+      for (int j = tid; j < J; j += kBlock) {
+        double s = lwj[j];
+        for (int l = 0; l < n; ++l) s += tile[l * pitch + j];
+        lwj[j] = s;
+      }
+      // log wtilde = sum_l log mean_j wbar_j(l): thread l takes cycle l's
+      // maximum, the block the exponentials, thread l their sum
+      double ml = -INFINITY;
+      if (tid < n)
+        for (int j = 0; j < J; ++j) ml = fmax(ml, tile[tid * pitch + j]);
+      __shared__ double row_max[kBlock];
+      row_max[tid] = ml;
+      __syncthreads();
+      for (int e = tid; e < n * J; e += kBlock) {
+        const int l = e / J, at = l * pitch + e % J;
+        tile[at] = exp(tile[at] - row_max[l]);
+      }
+      __syncthreads();
+      if (tid < n) {
+        double sl = 0.0;
+#pragma unroll 8
+        for (int j = 0; j < J; ++j) sl += tile[tid * pitch + j];
+        lt += (ml > -INFINITY) ? ml + log(sl / (double)J) : -INFINITY;
+      }
+    }
+    double m = -INFINITY;
+    for (int j = tid; j < J; j += kBlock) m = fmax(m, lwj[j]);
+    mx = block_reduce<OpMax<double>>(m, sh);
+    double r = 0.0;
+    for (int j = tid; j < J; j += kBlock) r += lwj[j] = exp(lwj[j] - mx);
+    rbar = block_reduce<OpSum<double>>(r, sh) / (double)J;
+    double q = 0.0;
+    for (int j = tid; j < J; j += kBlock) {
+      const double e = lwj[j] - rbar;
+      q = fma(e, e, q);
+    }
+    ss = block_reduce<OpSum<double>>(q, sh);
+  } else {
+    auto lw = [&](int j) {
+      double s = 0.0;
+      for (int l = 0; l < L; ++l) s += g[(int64_t)l * J + j];
+      return s;
+    };
+    double m = -INFINITY;
+    for (int j = tid; j < J; j += kBlock) m = fmax(m, lw(j));
+    mx = block_reduce<OpMax<double>>(m, sh);
+    double r = 0.0;
+    for (int j = tid; j < J; j += kBlock) r += exp(lw(j) - mx);
+    rbar = block_reduce<OpSum<double>>(r, sh) / (double)J;
+    double q = 0.0;
+    for (int j = tid; j < J; j += kBlock) {
+      const double e = exp(lw(j) - mx) - rbar;
+      q = fma(e, e, q);
+    }
+    ss = block_reduce<OpSum<double>>(q, sh);
+    for (int l = tid; l < L; l += kBlock) {
+      const double *gl = g + (int64_t)l * J;
+      double ml = -INFINITY;
+      for (int j = 0; j < J; ++j) ml = fmax(ml, gl[j]);
+      double sl = 0.0;
+      for (int j = 0; j < J; ++j) sl += exp(gl[j] - ml);
+      lt += (ml > -INFINITY) ? ml + log(sl / (double)J) : -INFINITY;
+    }
   }
   lt = block_reduce<OpSum<double>>(lt, sh);
   if (tid == 0) {
@@ -1509,22 +1601,17 @@ smc_status launch_adapt(const int64_t *n_accept, int64_t P, int32_t target_permi
 
 smc_status launch_rne(const double *theta, int32_t J, int32_t N, int32_t d, double *part,
                       double *rne, hipStream_t s) {
-  const int64_t P = (int64_t)J * N;
-  hipLaunchKernelGGL(k_rne_group, dim3(J), dim3(kBlock), 0, s, theta, P, N, d, part);
-  smc_status st = launch_status("rne/group");
-  if (st) return st;
-  hipLaunchKernelGGL(k_rne_final, dim3(1), dim3(64), 0, s, part, J, N, d, rne);
-  return launch_status("rne/final");
+  return launch_report(theta, J, N, d, part, nullptr, rne, s);
 }
 
 smc_status launch_report(const double *g, int32_t J, int32_t N, int32_t G, double *part,
                          double *out, double *rne_mean, hipStream_t s) {
   if (G < 1 || G > kDMax) return set_error(SMC_E_UNSUPPORTED, "report of %d functions", G);
   const int64_t P = (int64_t)J * N;
-  hipLaunchKernelGGL(k_rne_group, dim3(J), dim3(kBlock), 0, s, g, P, N, G, part);
+  hipLaunchKernelGGL(k_rne_group, dim3(J, G), dim3(kBlock), 0, s, g, P, N, part);
   smc_status st = launch_status("report/group");
   if (st) return st;
-  hipLaunchKernelGGL(k_report_final, dim3(1), dim3(64), 0, s, part, J, N, G, out, rne_mean);
+  hipLaunchKernelGGL(k_report_final, dim3(1), dim3(1024), 0, s, part, J, N, G, out, rne_mean);
   return launch_status("report/final");
 }
 
