@@ -175,6 +175,8 @@ struct Adjoint<Egarch<K, SH, R, I>> {
             ae += log2_fast(pm);
             pm = (R)1;
           }
+        } else if constexpr (Md::kTLog) {
+          ae += log1p_pos(Md::t_x(p, lastz, lastE));
         }
       }
       if constexpr (Md::kTProd) ae += log2_fast(pm);

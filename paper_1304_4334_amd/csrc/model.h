@@ -114,9 +114,47 @@ __device__ __forceinline__ double exp2_lean(double x) {
 __device__ __forceinline__ float log2_fast(float x) { return __builtin_amdgcn_logf(x); }
 __device__ __forceinline__ double log2_fast(double x) { return log2(x); }
 
-// Student-t kernel term log(1 + e^2/(nu - 2)): FP64 log1p; FP32 log2 (scaled
-// by ln 2 at the end).
-__device__ __forceinline__ double t_term(double e2, double inu2) { return log1p(e2 * inu2); }
+// log(1 + p) for p >= 0 (inf gives inf, NaN stays).  u = 1 + p with its
+// rounding error c kept (as c 2^-k, within 41% of c / u), u = 2^k m with m in
+// [sqrt(1/2), sqrt(2)), f = m - 1, and with s = f / (2 + f): log m = f - s (f - z Q(z)), z = s^2, Q the minimax
+// polynomial of kLog1pCoef (relative error 1.8e-18 with the coefficients
+// rounded to double; written by gen_log1p_coef.py).  The quotient is one
+// Newton step on the hardware reciprocal and a residual correction.  About 40
+// instructions against the library's 115; error within 2 ulp.
+constexpr double kSqrtHalf = 0x1.6a09e667f3bcdp-1;
+__device__ constexpr double kLog1pCoef[7] = {
+  0x1.5555555555592p-1,
+  0x1.999999997fdb8p-2,
+  0x1.24924941f1239p-2,
+  0x1.c71c52095e0b7p-3,
+  0x1.74663ee8431edp-3,
+  0x1.39a1babb1a6c1p-3,
+  0x1.2f05636381feep-3,
+};
+__device__ __forceinline__ double log1p_pos(double p) {
+  const double u = 1.0 + p, c = p - (u - 1.0);
+  const double m0 = __builtin_amdgcn_frexp_mant(u);
+  const int up = m0 < kSqrtHalf ? 1 : 0;
+  const double m = __builtin_ldexp(m0, up);
+  const int ki = __builtin_amdgcn_frexp_exp(u) - up;
+  const double k = (double)ki;
+  const double f = m - 1.0, d = 2.0 + f;
+  double r = __builtin_amdgcn_rcp(d);
+  r = fma(r, fma(-d, r, 1.0), r);
+  double s = f * r;
+  s = fma(fma(-d, s, f), r, s);
+  const double z = s * s;
+  double q = kLog1pCoef[6];
+#pragma unroll
+  for (int j = 5; j >= 0; --j) q = fma(q, z, kLog1pCoef[j]);
+  const double lo = fma(k, kLn2Lo, __builtin_ldexp(c, -ki));
+  const double v = fma(k, kLn2Hi, f - fma(s, fma(-z, q, f), -lo));
+  return p < INFINITY ? v : p;
+}
+
+// Student-t kernel term log(1 + e^2/(nu - 2)): FP64 natural; FP32 log2
+// (scaled by ln 2 at the end).
+__device__ __forceinline__ double t_term(double e2, double inu2) { return log1p_pos(e2 * inu2); }
 __device__ __forceinline__ float t_term(float e2, float inu2) {
   return __builtin_amdgcn_logf(fmaf(e2, inu2, 1.0f));
 }
@@ -235,7 +273,13 @@ struct Egarch {
   // time per observation than two).  A group whose product exceeds the float
   // range (four shocks in a row beyond about 6.6e4 (nu - 2)^(1/2) standard
   // deviations) counts as a zero density.
+  // FP64 Student-t shocks (kTLog): the factors 1 + x_i, x_i = eps_i^2/(nu - 2),
+  // of an accumulation group of 8 are multiplied as 1 + p, p <- p + x_i + p x_i
+  // (an add and an fma, so p keeps its relative precision however large nu
+  // is), before one log1p is taken; a group whose product leaves the range
+  // takes its factors' logarithms one by one (t_group_log).
   static constexpr bool kTProd = kT && sizeof(R_) == 4;
+  static constexpr bool kTLog = kT && sizeof(R_) == 8;
   static constexpr int kTGroup = 4;  // observations per log2 (divides kAcc)
   static_assert(kAcc % kTGroup == 0, "log2 groups inside accumulation groups");
   static constexpr bool kEps = sizeof(R_) == 4;  // the FP32 form of the step (see Par)
@@ -525,10 +569,32 @@ struct Egarch {
     else return z * E;
   }
 
+  // FP64 Student-t: x = eps^2/(nu - 2) from step()'s E and z, and the logarithm
+  // of a group's product from p = prod (1 + x_i) - 1.
+  __device__ __forceinline__ static R t_x(const Par &p, R z, R E) {
+    const R e = z * E;
+    return e * e * p.inu2;
+  }
+  template <int n>
+  __device__ __forceinline__ static R t_group_log(R p, const R (&x)[n]) {
+    R v = log1p_pos(p);
+    if (!(p < INFINITY)) {
+      v = (R)0;
+#pragma unroll
+      for (int i = 0; i < n; ++i) {
+        R xi = x[i];
+        __asm__ volatile("" : "+v"(xi));  // keeps this rare branch a branch
+        v += log1p_pos(xi);
+      }
+    }
+    return v;
+  }
+
   // One observation: returns the exponent sum used (for log h), adds eps^2
-  // (Gaussian), the Student-t term or the mixture's largest log2 term m to
-  // ae (and multiplies the mixture's sum of 2^(x_i - m) into pm), reports E
-  // and z (see shock()), and advances r to the next observation's exponents.
+  // (Gaussian) or the mixture's largest log2 term m to ae, multiplies the FP32
+  // Student-t factor or the mixture's sum of 2^(x_i - m) into pm (FP64
+  // Student-t: the caller takes x from E and z, see t_x), reports E and z (see
+  // shock()), and advances r to the next observation's exponents.
   __device__ __forceinline__ static R step(const Par &p, R y, Run &r, R &ae, R &pm, R &E_out,
                                            R &z_out) {
     const R sw = r.sw;
@@ -631,11 +697,7 @@ struct Egarch {
     }
     const R e = scaled(z) * Ef;
     const R E = scaled(Ef);
-    if constexpr (kTProd) {
-      pm *= fma(e * e, p.inu2, (R)1);  // the caller takes the log2 (see kTProd)
-    } else if constexpr (kT) {
-      ae += t_term(e * e, p.inu2);
-    } else if constexpr (kMix) {
+    if constexpr (kMix) {
       R x[I];
 #pragma unroll
       for (int i = 0; i < I; ++i) {
@@ -650,7 +712,7 @@ struct Egarch {
       for (int i = 1; i < I; ++i) sm += exp2_lean(x[i] - mx);
       ae += mx;
       pm *= sm;
-    } else {
+    } else if constexpr (!kT) {
       ae = fma(e, e, ae);
     }
     E_out = E;
@@ -698,6 +760,7 @@ struct Egarch {
       R ae = (R)0, pm = (R)1;
       const R sw = step(p, yv, r, ae, pm, E, z);
       if constexpr (kTProd) ae = log2_fast(pm);
+      if constexpr (kTLog) ae = log1p_pos(t_x(p, z, E));
       double ld;
       if constexpr (kT) ld = base + kLn2 * (double)sw - p.hnu1 * t_scale<R>() * (double)ae;
       else if constexpr (kMix) ld = base + kLn2 * ((double)sw + (double)ae + (double)log2_fast(pm));
@@ -772,6 +835,7 @@ struct Egarch {
     // every U, which halves the conversions and FP64 additions.
     constexpr int kF = sizeof(R) == 4 ? 2 : 1;  // groups per FP64 flush
     R av = (R)0, ae = (R)0, pm = (R)1;
+    R tx[kAcc];  // kTLog: the group's x_i
     auto flush = [&]() {
       sv += (double)av;
       se += (double)ae;
@@ -802,6 +866,11 @@ struct Egarch {
             ae += log2_fast(pm);
             pm = (R)1;
           }
+        }
+        if constexpr (kTLog) {
+          const R x = tx[pos] = t_x(p, zd, Ed);
+          pm = pos == 0 ? x : fma(pm, x, pm + x);
+          if (pos == kAcc - 1) ae = t_group_log(pm, tx);
         }
         if (pos == kAcc - 1 && (kF == 1 || odd)) flush();
       }
@@ -861,7 +930,12 @@ struct Egarch {
             pm = (R)1;
           }
         }
+        if constexpr (kTLog) {
+          const R x = tx[i] = t_x(p, zd, Ed);
+          pm = i == 0 ? x : fma(pm, x, pm + x);
+        }
       }
+      if constexpr (kTLog) ae = t_group_log(pm, tx);
       if (kF == 1 || (g & 1)) flush();
     }
     // an odd number of groups leaves the last one's span open
@@ -870,6 +944,7 @@ struct Egarch {
       R ae1 = (R)0, pm1 = (R)1, Ed, zd;
       const R av1 = step(p, *yp, r, ae1, pm1, Ed, zd);
       if constexpr (kTProd) ae1 = log2_fast(pm1);
+      if constexpr (kTLog) ae1 = log1p_pos(t_x(p, zd, Ed));
       sv += (double)av1;
       se += (double)ae1;
       if constexpr (kMix) se += (double)log2_fast(pm1);
@@ -881,6 +956,7 @@ struct Egarch {
     R ae1 = (R)0, pm1 = (R)1, E, z;
     const R av1 = step(p, *yp, r, ae1, pm1, E, z);
     if constexpr (kTProd) ae1 = log2_fast(pm1);
+    if constexpr (kTLog) ae1 = log1p_pos(t_x(p, z, E));
     sv += (double)av1;
     se += (double)ae1;
     if constexpr (kMix) se += (double)log2_fast(pm1);
