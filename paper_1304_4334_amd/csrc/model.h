@@ -571,9 +571,15 @@ struct Egarch {
 
   // FP64 Student-t: x = eps^2/(nu - 2) from step()'s E and z, and the logarithm
   // of a group's product from p = prod (1 + x_i) - 1.
+  // (contractions written out: every caller rounds alike)
   __device__ __forceinline__ static R t_x(const Par &p, R z, R E) {
+#pragma clang fp contract(off)
     const R e = z * E;
     return e * e * p.inu2;
+  }
+  __device__ __forceinline__ static R t_join(R p, R x) {
+#pragma clang fp contract(off)
+    return fma(p, x, p + x);
   }
   template <int n>
   __device__ __forceinline__ static R t_group_log(R p, const R (&x)[n]) {
@@ -869,7 +875,7 @@ struct Egarch {
         }
         if constexpr (kTLog) {
           const R x = tx[pos] = t_x(p, zd, Ed);
-          pm = pos == 0 ? x : fma(pm, x, pm + x);
+          pm = pos == 0 ? x : t_join(pm, x);
           if (pos == kAcc - 1) ae = t_group_log(pm, tx);
         }
         if (pos == kAcc - 1 && (kF == 1 || odd)) flush();
@@ -932,7 +938,7 @@ struct Egarch {
         }
         if constexpr (kTLog) {
           const R x = tx[i] = t_x(p, zd, Ed);
-          pm = i == 0 ? x : fma(pm, x, pm + x);
+          pm = i == 0 ? x : t_join(pm, x);
         }
       }
       if constexpr (kTLog) ae = t_group_log(pm, tx);

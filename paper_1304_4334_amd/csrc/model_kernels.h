@@ -628,6 +628,75 @@ constexpr size_t lds_bytes_of() {
   else return (size_t)Adjoint<M>::kLdsPerLane * 64 * sizeof(typename M::R);
 }
 
+// The same by the eight waves of a block (Adjoint::block_value_and_grad);
+// results in wave 0.
+template <class M>
+__device__ __forceinline__ double ll_and_grad_block(const typename M::Y *__restrict__ y,
+                                                    const double *th, int64_t t, void *ckpt,
+                                                    int64_t P, int64_t p, bool live, void *lds,
+                                                    double scale, double *g,
+                                                    typename M::R (&st)[Eval<M>::SR]) {
+  const auto par = M::params(th);
+  return Adjoint<M>::block_value_and_grad(par, th, t, y, typed<typename M::R>(ckpt), P, p, live,
+                                          lds, scale, g, st);
+}
+
+// Populations whose gradients go to blocks of eight waves.  A block takes most
+// of a compute unit's LDS, so more than 256 of them (16,384 particles) run in
+// turns while single waves still fill idle SIMDs.  Measured over 1,000
+// observations (blocks / single waves, us): EGARCH(2)-t FP32 111 / 250 at
+// 16,384, 208 / 253 at 32,768, and 250 for single waves up to 65,536; FP64 205
+// / 355 at 16,384 but 382 / 357 at 32,768; egarch_23 FP32 239 / 292 and FP64
+// 549 / 496 at 32,768.
+template <class M>
+constexpr int64_t kGradBlockMaxP = sizeof(typename M::R) == 4 ? 32768 : 16384;
+template <class M>
+constexpr bool grad_blocks() {
+  if constexpr (IsLinreg<M>::value) return false;
+  else return Adjoint<M>::kBlk;
+}
+constexpr int kGradThreads = 512;
+
+template <class M>
+__global__ void __launch_bounds__(kGradThreads)
+    k_loglik_backward_blk(int64_t P, const double *theta, int64_t t, const double *dloglik,
+                          double *dtheta, void *ckpt, const typename M::Y *__restrict__ y) {
+  extern __shared__ double lds_dyn[];
+  const int64_t p = blockIdx.x * 64ll + (threadIdx.x & 63);
+  const bool live = p < P;
+  const int64_t pc = live ? p : P - 1;
+  double th[M::D], g[M::D];
+#pragma unroll
+  for (int i = 0; i < M::D; ++i) {
+    th[i] = theta[i * P + pc];
+    g[i] = 0.0;
+  }
+  typename M::R st[Eval<M>::SR];
+  (void)ll_and_grad_block<M>(y, th, t, ckpt, P, pc, live, lds_dyn, dloglik[pc], g, st);
+  if (threadIdx.x < 64 && live)
+#pragma unroll
+    for (int i = 0; i < M::D; ++i) dtheta[i * P + p] = g[i];
+}
+
+template <class M>
+__global__ void __launch_bounds__(kGradThreads)
+    k_grad_post_blk(int64_t P, const double *theta, int64_t t, double *grad, void *ckpt,
+                    const typename M::Y *__restrict__ y) {
+  extern __shared__ double lds_dyn[];
+  const int64_t p = blockIdx.x * 64ll + (threadIdx.x & 63);
+  const bool live = p < P;
+  const int64_t pc = live ? p : P - 1;
+  double th[M::D], g[M::D];
+#pragma unroll
+  for (int i = 0; i < M::D; ++i) th[i] = theta[i * P + pc];
+  PriorGradOf<M>::run(th, g);
+  typename M::R st[Eval<M>::SR];
+  (void)ll_and_grad_block<M>(y, th, t, ckpt, P, pc, live, lds_dyn, 1.0, g, st);
+  if (threadIdx.x < 64 && live)
+#pragma unroll
+    for (int i = 0; i < M::D; ++i) grad[i * P + p] = g[i];
+}
+
 template <class M>
 __global__ void __launch_bounds__(64) k_loglik_backward(DevModel dm, int64_t P, const double *theta,
                                                         int64_t t, const double *dloglik,
@@ -670,51 +739,77 @@ __global__ void __launch_bounds__(64) k_grad_post(DevModel dm, int64_t P, const 
 // with (hL) w = theta - theta' - (1/2)(hL)(hL)' grad'.  ckpt: the adjoint's
 // checkpoint area of the population; lds: the block's LDS buffer.  Returns
 // whether the proposal was accepted (the particle's arrays are updated).
-template <class M>
+// kBlk: the eight waves of a block take one wave of particles together (the
+// gradient by block_value_and_grad); wave 0 proposes and decides, and lanes
+// that are not live repeat particle p and write nothing.
+template <class M, bool kBlk = false>
 __device__ __forceinline__ int mala_one(const DevModel &dm, int64_t P, int64_t p, int64_t t,
                                         double *theta, double *logprior, double *loglik,
                                         void *state, double *grad,
                                         const double *__restrict__ hchol, uint64_t seed,
                                         uint64_t run, uint64_t cycle, uint64_t iter, void *ckpt,
-                                        void *lds) {
+                                        void *lds, bool live = true,
+                                        const typename M::Y *__restrict__ ydata = nullptr) {
+  // contractions written out: the step rounds alike in every kernel that holds it
+#pragma clang fp contract(off)
   constexpr int D = M::D;
   using R = typename M::R;
   constexpr int SR = Eval<M>::SR;
   constexpr int SS = StoredS<M>::value;
+  const bool lead = !kBlk || threadIdx.x < 64;
   int acc = 0;
   double th[D], z[D], pr[D], g0[D], g1[D], u[D];
+  if (lead) {
 #pragma unroll
-  for (int i = 0; i < D; ++i) {
-    th[i] = theta[i * P + p];
-    g0[i] = grad[i * P + p];
-  }
-  normals<D>(seed, run, (uint64_t)p, cycle, iter, kProposal, z, D);
-  // u = (hL)' g0
-#pragma unroll
-  for (int k = 0; k < D; ++k) {
-    double s = 0.0;
-#pragma unroll
-    for (int i = k; i < D; ++i) s = fma(hchol[i * D + k], g0[i], s);
-    u[k] = s;
-  }
-#pragma unroll
-  for (int i = 0; i < D; ++i) {
-    double dr = 0.0, st = 0.0;
-#pragma unroll
-    for (int k = 0; k <= i; ++k) {
-      dr = fma(hchol[i * D + k], u[k], dr);
-      st = fma(hchol[i * D + k], z[k], st);
+    for (int i = 0; i < D; ++i) {
+      th[i] = theta[i * P + p];
+      g0[i] = grad[i * P + p];
     }
-    pr[i] = th[i] + 0.5 * dr + st;
+    normals<D>(seed, run, (uint64_t)p, cycle, iter, kProposal, z, D);
+    // u = (hL)' g0
+#pragma unroll
+    for (int k = 0; k < D; ++k) {
+      double s = 0.0;
+#pragma unroll
+      for (int i = k; i < D; ++i) s = fma(hchol[i * D + k], g0[i], s);
+      u[k] = s;
+    }
+#pragma unroll
+    for (int i = 0; i < D; ++i) {
+      double dr = 0.0, st = 0.0;
+#pragma unroll
+      for (int k = 0; k <= i; ++k) {
+        dr = fma(hchol[i * D + k], u[k], dr);
+        st = fma(hchol[i * D + k], z[k], st);
+      }
+      pr[i] = fma(0.5, dr, th[i]) + st;
+    }
+  }
+  if constexpr (kBlk) {  // the proposals to the block's other waves
+    double *sp = static_cast<double *>(lds) + (threadIdx.x & 63);
+    if (lead)
+#pragma unroll
+      for (int i = 0; i < D; ++i) sp[i * 64] = pr[i];
+    __syncthreads();
+    if (!lead)
+#pragma unroll
+      for (int i = 0; i < D; ++i) pr[i] = sp[i * 64];
+    __syncthreads();  // the area is reused
   }
   const double lp1 = M::logprior(pr);
   R stv[SR];
 #pragma unroll
   for (int k = 0; k < SR; ++k) stv[k] = (R)0;
   double ll1 = -INFINITY;
-  if (lp1 > -INFINITY) {
+  if (kBlk || lp1 > -INFINITY) {
     PriorGradOf<M>::run(pr, g1);
-    ll1 = ll_and_grad<M>(dm, pr, t, ckpt, P, p, lds, 1.0, g1, stv);
+    if constexpr (kBlk)
+      ll1 = ll_and_grad_block<M>(ydata, pr, t, ckpt, P, p, live, lds, 1.0, g1, stv);
+    else
+      ll1 = ll_and_grad<M>(dm, pr, t, ckpt, P, p, lds, 1.0, g1, stv);
+  }
+  if (!lead || !(lp1 > -INFINITY)) return 0;
+  {
     // reverse move
 #pragma unroll
     for (int k = 0; k < D; ++k) {
@@ -729,16 +824,17 @@ __device__ __forceinline__ int mala_one(const DevModel &dm, int64_t P, int64_t p
       double dr = 0.0;
 #pragma unroll
       for (int k = 0; k <= i; ++k) dr = fma(hchol[i * D + k], u[k], dr);
-      double a = th[i] - pr[i] - 0.5 * dr;
+      double a = fma(-0.5, dr, th[i] - pr[i]);
 #pragma unroll
       for (int k = 0; k < i; ++k) a = fma(-hchol[i * D + k], w[k], a);
       w[i] = a / hchol[i * D + i];
       ww = fma(w[i], w[i], ww);
       zz = fma(z[i], z[i], zz);
     }
-    const double delta = (lp1 + ll1) - (logprior[p] + loglik[p]) + (-0.5 * ww + 0.5 * zz);
+    const double delta =
+        (lp1 + ll1) - (logprior[p] + loglik[p]) + fma(0.5, zz, -0.5 * ww);
     const U64x4 wr = draw4(seed, run, (uint64_t)p, cycle, iter, kAccept);
-    acc = (log(u01_oo(wr.x0)) < delta) ? 1 : 0;
+    acc = (live && log(u01_oo(wr.x0)) < delta) ? 1 : 0;
   }
   if (acc) {
 #pragma unroll
@@ -769,6 +865,23 @@ __global__ void __launch_bounds__(64) k_mutate_mala(DevModel dm, int64_t P, int6
                       iter, ckpt, lds_dyn);
     if (accepted) accepted[p] = (uint8_t)acc;
   }
+  acc_store(dm.acc, __ballot(acc), blockIdx.x, P, n_accept);
+}
+
+template <class M>
+__global__ void __launch_bounds__(kGradThreads)
+    k_mutate_mala_blk(DevModel dm, int64_t P, int64_t t, double *theta, double *logprior,
+                      double *loglik, void *state, double *grad, const double *__restrict__ hchol,
+                      uint64_t seed, uint64_t run, uint64_t cycle, uint64_t iter,
+                      unsigned long long *n_accept, uint8_t *accepted, void *ckpt,
+                      const typename M::Y *__restrict__ y) {
+  extern __shared__ double lds_dyn[];
+  const int64_t p = blockIdx.x * 64ll + (threadIdx.x & 63);
+  const bool live = p < P;
+  const int acc = mala_one<M, true>(dm, P, live ? p : P - 1, t, theta, logprior, loglik, state,
+                                    grad, hchol, seed, run, cycle, iter, ckpt, lds_dyn, live, y);
+  if (threadIdx.x >= 64) return;
+  if (accepted && live) accepted[p] = (uint8_t)acc;
   acc_store(dm.acc, __ballot(acc), blockIdx.x, P, n_accept);
 }
 
@@ -886,6 +999,14 @@ struct OpsOf {
     if constexpr (!HasAdjoint<M>::value) {
       return set_error(SMC_E_UNSUPPORTED, "no adjoint for normal-mixture shocks");
     } else {
+      if constexpr (grad_blocks<M>()) {
+        if (P <= kGradBlockMaxP<M>) {
+          hipLaunchKernelGGL(k_loglik_backward_blk<M>, grid_for(P, 64), dim3(kGradThreads),
+                             Adjoint<M>::kBlkLds, s, P, theta, t, dloglik, dtheta, ckpt,
+                             Eval<M>::host_y(m));
+          return launch_status("loglik_backward");
+        }
+      }
       hipLaunchKernelGGL(k_loglik_backward<M>, grid_for(P, 64), dim3(64), lds_bytes_of<M>(), s, m,
                          P, theta, t, dloglik, dtheta, ckpt);
       return launch_status("loglik_backward");
@@ -897,6 +1018,13 @@ struct OpsOf {
     if constexpr (!HasAdjoint<M>::value) {
       return set_error(SMC_E_UNSUPPORTED, "no adjoint for normal-mixture shocks");
     } else {
+      if constexpr (grad_blocks<M>()) {
+        if (P <= kGradBlockMaxP<M>) {
+          hipLaunchKernelGGL(k_grad_post_blk<M>, grid_for(P, 64), dim3(kGradThreads),
+                             Adjoint<M>::kBlkLds, s, P, theta, t, grad, ckpt, Eval<M>::host_y(m));
+          return launch_status("posterior_grad");
+        }
+      }
       hipLaunchKernelGGL(k_grad_post<M>, grid_for(P, 64), dim3(64), lds_bytes_of<M>(), s, m, P,
                          theta, t, grad, ckpt);
       return launch_status("posterior_grad");
@@ -920,6 +1048,16 @@ struct OpsOf {
     if constexpr (!HasAdjoint<M>::value) {
       return set_error(SMC_E_UNSUPPORTED, "no adjoint for normal-mixture shocks");
     } else {
+      if constexpr (grad_blocks<M>()) {
+        if (P <= kGradBlockMaxP<M>) {
+          hipLaunchKernelGGL(k_mutate_mala_blk<M>, grid_for(P, 64), dim3(kGradThreads),
+                             Adjoint<M>::kBlkLds, s, m, P, t, theta, logprior, loglik, state, grad,
+                             hchol, seed, run, cycle, iter,
+                             reinterpret_cast<unsigned long long *>(n_accept), accepted, ckpt,
+                             Eval<M>::host_y(m));
+          return launch_status("mutate/mala");
+        }
+      }
       hipLaunchKernelGGL(k_mutate_mala<M>, grid_for(P, 64), dim3(64), lds_bytes_of<M>(), s, m, P,
                          t, theta, logprior, loglik, state, grad, hchol, seed, run, cycle, iter,
                          reinterpret_cast<unsigned long long *>(n_accept), accepted, ckpt);
