@@ -1322,7 +1322,8 @@ smc_status launch_mutate_rw(const DevModel &m, int64_t P, int64_t t, double *the
                             uint64_t seed, uint64_t run, uint64_t cycle, uint64_t iter,
                             int64_t *n_accept, uint8_t *accepted, hipStream_t s,
                             const KernelTimer *timer, const MomFuse *fuse) {
-  const bool shaped = (m.block != 0 && m.block != 64) || (m.unroll != 0 && m.unroll != kUnroll);
+  const bool shaped = !split_density(m, P) &&
+                      ((m.block != 0 && m.block != 64) || (m.unroll != 0 && m.unroll != kUnroll));
   if (shaped && m.shock == SMC_SHOCK_MIXTURE) {
     return m.prec == SMC_FP32
                ? launch_mutate_rw_shaped_mix32(m, P, t, theta, logprior, loglik, state, hchol,

@@ -232,6 +232,19 @@ int32_t num_test_fns(const DevModel &m, int32_t which);  // -1 if unsupported
 smc_status launch_test_fns(const DevModel &m, int64_t P, const double *theta, const void *state,
                            int64_t t, int32_t which, double *out, hipStream_t s);
 
+// Whether the likelihoods of P particles go to blocks of four waves, one for
+// the recursion and three for the density (Egarch::advance_split): families
+// with a heavy density, up to the population that fills the chip's SIMDs that
+// way.  Likelihoods over 1,000 observations, blocks at 32,768 vectors against
+// single waves at 32,832 (us): egarch_23 FP64 150 / 209, FP32 54 / 72,
+// egarch_12 FP64 112 / 162, EGARCH(2)-t FP64 89 / 90 (77 at 4,096); with
+// 65,536 vectors single waves fill the SIMDs themselves.
+constexpr int64_t kSplitMaxP = 32768;
+inline bool split_density(const DevModel &m, int64_t P) {
+  return P <= kSplitMaxP && (m.shock == SMC_SHOCK_MIXTURE ||
+                             (m.shock == SMC_SHOCK_STUDENT_T && m.prec == SMC_FP64));
+}
+
 // Bytes of the adjoint checkpoints of P particles over t observations.
 size_t adjoint_ckpt_bytes(const DevModel &m, int64_t P, int64_t t);
 smc_status launch_loglik_backward(const DevModel &m, int64_t P, const double *theta, int64_t t,

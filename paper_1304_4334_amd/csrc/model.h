@@ -596,6 +596,27 @@ struct Egarch {
     return v;
   }
 
+  // Mixture density of eps = z E: its largest log2 term m is added to ae, its
+  // sum of 2^(x_i - m) multiplied into pm.  (eps - mu_i is one fma of z and E.)
+  __device__ __forceinline__ static void density(const Par &p, R z, R E, R &ae, R &pm) {
+    if constexpr (kMix) {
+      R x[I];
+#pragma unroll
+      for (int i = 0; i < I; ++i) {
+        const R dd = fma(z, E, -p.mu[i]);
+        x[i] = fma(p.nb[i] * dd, dd, p.lw[i]);
+      }
+      R mx = x[0];
+#pragma unroll
+      for (int i = 1; i < I; ++i) mx = fmax(mx, x[i]);
+      R sm = exp2_lean(x[0] - mx);
+#pragma unroll
+      for (int i = 1; i < I; ++i) sm += exp2_lean(x[i] - mx);
+      ae += mx;
+      pm *= sm;
+    }
+  }
+
   // One observation: returns the exponent sum used (for log h), adds eps^2
   // (Gaussian) or the mixture's largest log2 term m to ae, multiplies the FP32
   // Student-t factor or the mixture's sum of 2^(x_i - m) into pm (FP64
@@ -618,20 +639,7 @@ struct Egarch {
       if constexpr (kTProd) {
         pm *= fma(e, e, (R)1);  // 1 + eps^2/(nu - 2); the caller takes the log2
       } else if constexpr (kMix) {
-        R x[I];
-#pragma unroll
-        for (int i = 0; i < I; ++i) {
-          const R dd = e - p.mu[i];
-          x[i] = fma(p.nb[i] * dd, dd, p.lw[i]);
-        }
-        R mx = x[0];
-#pragma unroll
-        for (int i = 1; i < I; ++i) mx = fmax(mx, x[i]);
-        R sm = exp2_lean(x[0] - mx);
-#pragma unroll
-        for (int i = 1; i < I; ++i) sm += exp2_lean(x[i] - mx);
-        ae += mx;
-        pm *= sm;
+        density(p, zq, Ef, ae, pm);
       } else {
         ae = fma(e, e, ae);
       }
@@ -701,27 +709,13 @@ struct Egarch {
     } else {
       r.sw = fma(scaled(kk), Ef, AA);
     }
-    const R e = scaled(z) * Ef;
-    const R E = scaled(Ef);
     if constexpr (kMix) {
-      R x[I];
-#pragma unroll
-      for (int i = 0; i < I; ++i) {
-        const R dd = e - p.mu[i];
-        x[i] = fma(p.nb[i] * dd, dd, p.lw[i]);
-      }
-      R mx = x[0];
-#pragma unroll
-      for (int i = 1; i < I; ++i) mx = fmax(mx, x[i]);
-      R sm = exp2_lean(x[0] - mx);
-#pragma unroll
-      for (int i = 1; i < I; ++i) sm += exp2_lean(x[i] - mx);
-      ae += mx;
-      pm *= sm;
+      density(p, scaled(z), Ef, ae, pm);
     } else if constexpr (!kT) {
+      const R e = z * Ef;
       ae = fma(e, e, ae);
     }
-    E_out = E;
+    E_out = scaled(Ef);
     z_out = z;
     return sw;
   }
@@ -816,6 +810,79 @@ struct Egarch {
     st[K] = shock(p, z, E);
   }
 
+  // The rest of advance() and advance_split() from group g0 of kAcc on: whole
+  // groups, single observations, and the last one, whose exponents and shock
+  // give the state.
+  __device__ __forceinline__ static double finish(const Par &p, R (&st)[S], Run &r,
+                                                  const Y *__restrict__ yp, int n, int g0, R av,
+                                                  R ae, R pm, double sv, double se) {
+    const R kap = (R)kKappa;
+    const int nm = n - 1, nb = nm / kAcc;
+    constexpr int kF = sizeof(R) == 4 ? 2 : 1;
+    R tx[kAcc];
+    auto flush = [&]() {
+      sv += (double)av;
+      se += (double)ae;
+      if constexpr (kMix) se += (double)log2_fast(pm);
+      ae = (R)0;
+      pm = (R)1;
+    };
+    for (int g = g0; g < nb; ++g, yp += kAcc) {
+      R yb[kAcc];
+#pragma unroll
+      for (int i = 0; i < kAcc; ++i) yb[i] = yp[i];
+#pragma unroll
+      for (int i = 0; i < kAcc; ++i) {
+        R Ed, zd;
+        const R sw = step(p, yb[i], r, ae, pm, Ed, zd);
+        if (i == 0 && (kF == 1 || !(g & 1))) av = sw;
+        else av += sw;
+        if constexpr (kTProd) {
+          if (i % kTGroup == kTGroup - 1) {
+            ae += log2_fast(pm);
+            pm = (R)1;
+          }
+        }
+        if constexpr (kTLog) {
+          const R x = tx[i] = t_x(p, zd, Ed);
+          pm = i == 0 ? x : t_join(pm, x);
+        }
+      }
+      if constexpr (kTLog) ae = t_group_log(pm, tx);
+      if (kF == 1 || (g & 1)) flush();
+    }
+    // an odd number of groups leaves the last one's span open
+    if (kF == 2 && (nb & 1)) flush();
+    for (int i = nb * kAcc; i < nm; ++i, ++yp) {
+      R ae1 = (R)0, pm1 = (R)1, Ed, zd;
+      const R av1 = step(p, *yp, r, ae1, pm1, Ed, zd);
+      if constexpr (kTProd) ae1 = log2_fast(pm1);
+      if constexpr (kTLog) ae1 = log1p_pos(t_x(p, zd, Ed));
+      sv += (double)av1;
+      se += (double)ae1;
+      if constexpr (kMix) se += (double)log2_fast(pm1);
+    }
+    // The last observation: keep its exponents and shock for the state.
+    R wl[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) wl[k] = r.w[k];
+    R ae1 = (R)0, pm1 = (R)1, E, z;
+    const R av1 = step(p, *yp, r, ae1, pm1, E, z);
+    if constexpr (kTProd) ae1 = log2_fast(pm1);
+    if constexpr (kTLog) ae1 = log1p_pos(t_x(p, z, E));
+    sv += (double)av1;
+    se += (double)ae1;
+    if constexpr (kMix) se += (double)log2_fast(pm1);
+#pragma unroll
+    for (int k = 0; k < K; ++k) st[k] = wl[k] / kap;
+    st[K] = shock(p, z, E);
+    const double nd = (double)n;
+    // log h_s = log sigma_Y - ln2 * sum_k w_ks
+    if constexpr (kT) return nd * (p.cst - p.lsig) + kLn2 * sv - p.hnu1 * t_scale<R>() * se;
+    else if constexpr (kMix) return nd * (p.cst - p.lsig) + kLn2 * (sv + se);
+    else return nd * (p.cst - p.lsig) + kLn2 * sv - 0.5 * se;
+  }
+
   // Sum of log p(y_s | y_{1:s-1}, theta) over s = t0+1..t1.  st holds the
   // state at t0 in the API's units, (v_1..v_K, eps_t0), and receives the
   // state at t1.  The terms are summed in groups of kAcc; the observations
@@ -828,7 +895,6 @@ struct Egarch {
     static_assert(U == 4 || U == 8 || U == 16, "batches of 4, 8 or 16 observations");
     if (t1 <= t0) return 0.0;
     Run r;
-    const R kap = (R)kKappa;
     start(p, st, t0, r);
     double sv = 0.0, se = 0.0;
     const Y *yp = y + t0;
@@ -918,62 +984,125 @@ struct Egarch {
         yp += U;
       }
     }
-    // a group left over by batches of 16 (group 2j, as nbat batches of 16
-    // hold an even number of groups)
-    for (int g = nbat * Q / G; g < nb; ++g, yp += kAcc) {
-      R yb[kAcc];
+    return finish(p, st, r, yp, n, nbat * Q / G, av, ae, pm, sv, se);
+  }
+
+  // advance() by a block of four waves that hold the same particles, for
+  // families whose density is most of the work (mixtures: two thirds of the
+  // instructions of an observation; FP64 Student-t: a quarter) and
+  // populations that leave SIMDs idle.  Wave 0 runs the recursion and leaves z
+  // and E of every observation in LDS; waves 1 to 3 evaluate the density, a
+  // whole accumulation span each per stage of three spans, a stage behind.
+  // The spans' sums are added in order (by wave 1), so the result is
+  // advance()'s to the bit; it is valid in wave 0, st too.  Bound by the
+  // recursion wave's issue: 32 instructions per observation for egarch_23
+  // FP64 against 100 of the whole (300 vectors over 777 observations: 151 us by
+  // one wave per 64 vectors, 67 by blocks).
+  static constexpr bool kSplitOk = kMix || kTLog;
+  static constexpr int kDens = 3;                                   // density waves
+  static constexpr int kSpan = kAcc * (sizeof(R) == 4 ? 2 : 1);     // observations of a span
+  static constexpr int kStage = kDens * kSpan;
+  static constexpr int kSplitThreads = 64 * (kDens + 1);
+  // LDS: [2][kStage][2][64] R (z, E), [2][kDens][2][64] doubles (span sums)
+  static constexpr size_t kSplitLds =
+      (size_t)64 * (2 * kStage * 2 * sizeof(R) + 2 * kDens * 2 * sizeof(double));
+  __device__ static double advance_split(const Par &p, R (&st)[S], int64_t t0, int64_t t1,
+                                         const Y *__restrict__ y, void *lds) {
+    if (t1 <= t0) return 0.0;
+    const int lane = threadIdx.x & 63;
+    const int role = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    R *ring = static_cast<R *>(lds) + lane;
+    double *sums = reinterpret_cast<double *>(static_cast<R *>(lds) + 2 * kStage * 2 * 64) + lane;
+    const int n = (int)(t1 - t0), nst = (n - 1) / kStage;  // whole stages before the last date
+    auto barrier = [] {
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+      __builtin_amdgcn_s_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+    };
+    double sv = 0.0, se = 0.0;
+    Run r;
+    if (role == 0) {
+      start(p, st, t0, r);
+      const Y *yp = y + t0;
+      Y yn[kAcc];
+      if (nst > 0)
 #pragma unroll
-      for (int i = 0; i < kAcc; ++i) yb[i] = yp[i];
+        for (int u = 0; u < kAcc; ++u) yn[u] = yp[u];
+      for (int i = 0; i < nst; ++i) {
+        R *o = ring + (i & 1) * (kStage * 2 * 64);
+        R av = (R)0;
 #pragma unroll
-      for (int i = 0; i < kAcc; ++i) {
-        R Ed, zd;
-        const R sw = step(p, yb[i], r, ae, pm, Ed, zd);
-        if (i == 0 && (kF == 1 || !(g & 1))) av = sw;
-        else av += sw;
-        if constexpr (kTProd) {
-          if (i % kTGroup == kTGroup - 1) {
-            ae += log2_fast(pm);
-            pm = (R)1;
+        for (int g = 0; g < kStage / kAcc; ++g) {
+          Y yb[kAcc];
+#pragma unroll
+          for (int u = 0; u < kAcc; ++u) yb[u] = yn[u];
+          yp += kAcc;
+          const Y *__restrict__ pn = i == nst - 1 && g == kStage / kAcc - 1 ? y + t0 : yp;
+#pragma unroll
+          for (int u = 0; u < kAcc; ++u) yn[u] = pn[u];
+#pragma unroll
+          for (int u = 0; u < kAcc; ++u) {
+            R ae = (R)0, pm = (R)1, E, z;  // not used: the density goes elsewhere
+            const R sw = step(p, yb[u], r, ae, pm, E, z);
+            const int j = g * kAcc + u;
+            o[(j * 2) * 64] = z;
+            o[(j * 2 + 1) * 64] = E;
+            av = j % kSpan == 0 ? sw : av + sw;
+            if (j % kSpan == kSpan - 1) sv += (double)av;
           }
         }
-        if constexpr (kTLog) {
-          const R x = tx[i] = t_x(p, zd, Ed);
-          pm = i == 0 ? x : t_join(pm, x);
+        barrier();
+      }
+      if (nst > 0) {
+        barrier();
+        barrier();
+        se = sums[0];
+      }
+      return finish(p, st, r, y + t0 + (int64_t)nst * kStage, n, nst * (kStage / kAcc), (R)0,
+                    (R)0, (R)1, sv, se);
+    }
+    for (int i = 0; i < nst + 1; ++i) {
+      if (role == 1 && i >= 2) {  // the sums of stage i - 2
+        const double *q = sums + ((i - 2) & 1) * (kDens * 2 * 64);
+#pragma unroll
+        for (int d = 0; d < kDens; ++d) {
+          se += q[(d * 2) * 64];
+          if constexpr (kMix) se += q[(d * 2 + 1) * 64];
         }
       }
-      if constexpr (kTLog) ae = t_group_log(pm, tx);
-      if (kF == 1 || (g & 1)) flush();
-    }
-    // an odd number of groups leaves the last one's span open
-    if (kF == 2 && (nb & 1)) flush();
-    for (int i = nb * kAcc; i < nm; ++i, ++yp) {
-      R ae1 = (R)0, pm1 = (R)1, Ed, zd;
-      const R av1 = step(p, *yp, r, ae1, pm1, Ed, zd);
-      if constexpr (kTProd) ae1 = log2_fast(pm1);
-      if constexpr (kTLog) ae1 = log1p_pos(t_x(p, zd, Ed));
-      sv += (double)av1;
-      se += (double)ae1;
-      if constexpr (kMix) se += (double)log2_fast(pm1);
-    }
-    // The last observation: keep its exponents and shock for the state.
-    R wl[K];
+      if (i >= 1) {
+        const R *o = ring + ((i - 1) & 1) * (kStage * 2 * 64) + (role - 1) * (kSpan * 2 * 64);
+        R ae = (R)0, pm = (R)1, tx[kAcc];
 #pragma unroll
-    for (int k = 0; k < K; ++k) wl[k] = r.w[k];
-    R ae1 = (R)0, pm1 = (R)1, E, z;
-    const R av1 = step(p, *yp, r, ae1, pm1, E, z);
-    if constexpr (kTProd) ae1 = log2_fast(pm1);
-    if constexpr (kTLog) ae1 = log1p_pos(t_x(p, z, E));
-    sv += (double)av1;
-    se += (double)ae1;
-    if constexpr (kMix) se += (double)log2_fast(pm1);
+        for (int u = 0; u < kSpan; ++u) {
+          const R z = o[(u * 2) * 64], E = o[(u * 2 + 1) * 64];
+          if constexpr (kMix) {
+            density(p, z, E, ae, pm);
+          } else {
+            const R x = tx[u % kAcc] = t_x(p, z, E);
+            pm = u % kAcc == 0 ? x : t_join(pm, x);
+          }
+        }
+        if constexpr (kTLog) ae = t_group_log(pm, tx);
+        double *q = sums + ((i - 1) & 1) * (kDens * 2 * 64) + (role - 1) * (2 * 64);
+        q[0] = (double)ae;
+        if constexpr (kMix) q[64] = (double)log2_fast(pm);
+      }
+      if (nst > 0) barrier();
+    }
+    if (nst > 0) {
+      if (role == 1) {
+        const double *q = sums + ((nst - 1) & 1) * (kDens * 2 * 64);
 #pragma unroll
-    for (int k = 0; k < K; ++k) st[k] = wl[k] / kap;
-    st[K] = shock(p, z, E);
-    const double nd = (double)n;
-    // log h_s = log sigma_Y - ln2 * sum_k w_ks
-    if constexpr (kT) return nd * (p.cst - p.lsig) + kLn2 * sv - p.hnu1 * t_scale<R>() * se;
-    else if constexpr (kMix) return nd * (p.cst - p.lsig) + kLn2 * (sv + se);
-    else return nd * (p.cst - p.lsig) + kLn2 * sv - 0.5 * se;
+        for (int d = 0; d < kDens; ++d) {
+          se += q[(d * 2) * 64];
+          if constexpr (kMix) se += q[(d * 2 + 1) * 64];
+        }
+        sums[0] = se;
+      }
+      barrier();
+    }
+    return 0.0;
   }
 };
 
@@ -984,6 +1113,7 @@ template <int NREG>
 struct Linreg {
   static constexpr int D = NREG + 1;
   static constexpr int S = 1;  // unused placeholder (no recursion state)
+  static constexpr bool kSplitOk = false;
   using R = double;
   using Y = double;
   static constexpr double kA0 = 2.0, kB0 = 1.0, kC0 = 100.0;

@@ -343,8 +343,26 @@ __device__ __forceinline__ bool fused_scale(const MomFuse &fm, int64_t P, double
 template <int B>
 constexpr bool scale_wave() { return B >= 256; }
 
-template <class M, int B = 64, int U = kUnroll>
-__global__ void __launch_bounds__(scale_wave<B>() ? B + 64 : B) k_mutate_rw(DevModel dm, int64_t P,
+//
+// kSplit (B = 64): three more waves evaluate the particle wave's densities
+// (Egarch::advance_split); it hands them its proposals in LDS.
+template <class M, bool kSplit>
+constexpr int split_threads() {
+  if constexpr (kSplit) return M::kSplitThreads;
+  else return 0;
+}
+template <class M, int B, bool kSplit>
+constexpr int rw_threads() {
+  return kSplit ? split_threads<M, kSplit>() : (scale_wave<B>() ? B + 64 : B);
+}
+template <class M>
+constexpr size_t split_lds(bool proposals) {
+  if constexpr (M::kSplitOk) return M::kSplitLds + (proposals ? M::D * 64 * sizeof(double) : 0);
+  else return 0;
+}
+
+template <class M, int B = 64, int U = kUnroll, bool kSplit = false>
+__global__ void __launch_bounds__((rw_threads<M, B, kSplit>())) k_mutate_rw(DevModel dm, int64_t P,
                                                                             int64_t t,
                                                       double *theta,
                                                  double *logprior, double *loglik, void *state,
@@ -390,6 +408,21 @@ __global__ void __launch_bounds__(scale_wave<B>() ? B + 64 : B) k_mutate_rw(DevM
       return;
     }
   }
+  static_assert(!kSplit || B == 64, "one particle wave per split block");
+  extern __shared__ double lds_dyn[];
+  if constexpr (kSplit) {
+    if (threadIdx.x >= 64) {  // a density wave
+      if (fm.part) __syncthreads();
+      __syncthreads();
+      const double *sp = lds_dyn + M::kSplitLds / 8 + (threadIdx.x & 63);
+      double pr[D];
+#pragma unroll
+      for (int i = 0; i < D; ++i) pr[i] = sp[i * 64];
+      R st[SR];
+      (void)M::advance_split(M::params(pr), st, 0, t, ydata, lds_dyn);
+      return;
+    }
+  }
   const int64_t p = blockIdx.x * (int64_t)B + threadIdx.x;
   const int64_t pc = p < P ? p : P - 1;
   // without a scaling wave, the first particle wave's scale loads go first,
@@ -419,7 +452,7 @@ __global__ void __launch_bounds__(scale_wave<B>() ? B + 64 : B) k_mutate_rw(DevM
     }
   }
   int acc = 0;
-  if (p < P) {
+  if (kSplit || p < P) {
     double pr[D];
     if (fused) {
       // h L rounded as the moments kernels round it: h * L_ik (0 without a factor)
@@ -445,9 +478,18 @@ __global__ void __launch_bounds__(scale_wave<B>() ? B + 64 : B) k_mutate_rw(DevM
 #pragma unroll
     for (int k = 0; k < SR; ++k) st[k] = (R)0;
     double ll1 = -INFINITY;
-    if (lp1 > -INFINITY) {
-      const auto par = M::params(pr);
-      ll1 = Eval<M>::template advance_y<U>(dm, ydata, par, st, 0, t);
+    if constexpr (kSplit) {  // all lanes take part, those without a particle too
+      double *sp = lds_dyn + M::kSplitLds / 8 + threadIdx.x;
+#pragma unroll
+      for (int i = 0; i < D; ++i) sp[i * 64] = pr[i];
+      __syncthreads();
+      ll1 = M::advance_split(M::params(pr), st, 0, t, ydata, lds_dyn);
+    }
+    if (lp1 > -INFINITY && (!kSplit || p < P)) {
+      if constexpr (!kSplit) {
+        const auto par = M::params(pr);
+        ll1 = Eval<M>::template advance_y<U>(dm, ydata, par, st, 0, t);
+      }
       const double delta = (lp1 + ll1) - (logprior[p] + loglik[p]);
       const U64x4 w = draw4(seed, run, (uint64_t)p, cycle, iter, kAccept);
       acc = (log(u01_oo(w.x0)) < delta) ? 1 : 0;
@@ -460,13 +502,13 @@ __global__ void __launch_bounds__(scale_wave<B>() ? B + 64 : B) k_mutate_rw(DevM
 #pragma unroll
       for (int k = 0; k < SS; ++k) typed<R>(state)[k * P + p] = st[k];
     }
-    if (accepted) accepted[p] = (uint8_t)acc;
+    if (accepted && (!kSplit || p < P)) accepted[p] = (uint8_t)acc;
   }
   acc_store(dm.acc, __ballot(acc), (blockIdx.x * (int64_t)B + threadIdx.x) >> 6, P, n_accept);
 }
 
 // Launch of the random-walk step in shape (B, U).
-template <class M, int B, int U>
+template <class M, int B, int U, bool kSplit = false>
 smc_status launch_rw_shape(const DevModel &m, int64_t P, int64_t t, double *theta,
                            double *logprior, double *loglik, void *state, const double *hchol,
                            uint64_t seed, uint64_t run, uint64_t cycle, uint64_t iter,
@@ -479,13 +521,15 @@ smc_status launch_rw_shape(const DevModel &m, int64_t P, int64_t t, double *thet
     fm = *fuse;
   }
   const typename M::Y *yd = Eval<M>::host_y(m);
-  const dim3 threads(fm.part && scale_wave<B>() ? B + 64 : B);  // a folded scale's scaling wave
+  // a folded scale's scaling wave, or the density waves
+  const dim3 threads(kSplit || (fm.part && scale_wave<B>()) ? rw_threads<M, B, kSplit>() : B);
+  const size_t lds = kSplit ? split_lds<M>(true) : 0;
   if (timer)
-    hipExtLaunchKernelGGL((k_mutate_rw<M, B, U>), grid_for(P, B), threads, 0, s, timer->start,
+    hipExtLaunchKernelGGL((k_mutate_rw<M, B, U, kSplit>), grid_for(P, B), threads, lds, s, timer->start,
                           timer->stop, 0, m, P, t, theta, logprior, loglik, state, hchol, seed,
                           run, cycle, iter, acc, accepted, fm, yd);
   else
-    hipLaunchKernelGGL((k_mutate_rw<M, B, U>), grid_for(P, B), threads, 0, s, m, P, t, theta,
+    hipLaunchKernelGGL((k_mutate_rw<M, B, U, kSplit>), grid_for(P, B), threads, lds, s, m, P, t, theta,
                        logprior, loglik, state, hchol, seed, run, cycle, iter, acc, accepted, fm,
                        yd);
   return launch_status("mutate");
@@ -595,6 +639,28 @@ __global__ void __launch_bounds__(64) k_loglik(DevModel dm, int64_t P, const dou
   if (state_out)
 #pragma unroll
     for (int k = 0; k < StoredS<M>::value; ++k) typed<R>(state_out)[k * P + p] = st[k];
+}
+
+template <class M>
+__global__ void __launch_bounds__((split_threads<M, true>()))
+    k_loglik_split(int64_t P, const double *theta, int64_t t, double *out, void *state_out,
+                   const typename M::Y *__restrict__ ydata) {
+  extern __shared__ double lds_dyn[];
+  const int64_t p = blockIdx.x * 64ll + (threadIdx.x & 63);
+  const int64_t pc = p < P ? p : P - 1;
+  using R = typename M::R;
+  double th[M::D];
+#pragma unroll
+  for (int i = 0; i < M::D; ++i) th[i] = theta[i * P + pc];
+  R st[M::S];
+#pragma unroll
+  for (int k = 0; k < M::S; ++k) st[k] = (R)0;
+  const double ll = M::advance_split(M::params(th), st, 0, t, ydata, lds_dyn);
+  if (threadIdx.x >= 64 || p >= P) return;
+  out[p] = ll;
+  if (state_out)
+#pragma unroll
+    for (int k = 0; k < M::S; ++k) typed<R>(state_out)[k * P + p] = st[k];
 }
 
 // ------------------------------------- gradients and the Langevin step (a8) --
@@ -954,6 +1020,11 @@ struct OpsOf {
                               uint64_t seed, uint64_t run, uint64_t cycle, uint64_t iter,
                               int64_t *n_accept, uint8_t *accepted, const KernelTimer *timer,
                               const MomFuse *fuse, hipStream_t s) {
+    if constexpr (M::kSplitOk)
+      if (split_density(m, P))
+        return launch_rw_shape<M, 64, kUnroll, true>(m, P, t, theta, logprior, loglik, state, hchol,
+                                                     seed, run, cycle, iter, n_accept, accepted,
+                                                     timer, fuse, s);
     return launch_rw_shape<M, 64, kUnroll>(m, P, t, theta, logprior, loglik, state, hchol, seed,
                                            run, cycle, iter, n_accept, accepted, timer, fuse, s);
   }
@@ -978,6 +1049,12 @@ struct OpsOf {
 
   static smc_status loglik(const DevModel &m, int64_t P, const double *theta, int64_t t,
                            double *out, void *state_out, hipStream_t s) {
+    if constexpr (M::kSplitOk)
+      if (split_density(m, P)) {
+        hipLaunchKernelGGL(k_loglik_split<M>, grid_for(P, 64), dim3(M::kSplitThreads),
+                           split_lds<M>(false), s, P, theta, t, out, state_out, Eval<M>::host_y(m));
+        return launch_status("loglik");
+      }
     hipLaunchKernelGGL(k_loglik<M>, grid_for(P, 64), dim3(64), 0, s, m, P, theta, t, out,
                        state_out);
     return launch_status("loglik");
