@@ -233,6 +233,20 @@ smc_status smc_loglik_backward(const smc_model *m, int64_t P, const double *thet
                                size_t ws_bytes, void *stream);
 size_t smc_backward_ws_bytes(const smc_model *m, int64_t P, int64_t t);
 
+/* The same pair for callers that need both the value and its gradient:
+ * smc_loglik_ckpt is smc_loglik (the same values, to the bit) that also
+ * leaves the adjoint's checkpoints in ckpt (device, 8-byte aligned, >=
+ * smc_loglik_ckpt_bytes bytes), and smc_loglik_backward_ckpt takes the
+ * gradient from them without running the recursion forward again.  It only
+ * reads ckpt, so it may be called several times; model, P, theta and t must be
+ * those of the smc_loglik_ckpt call. */
+size_t smc_loglik_ckpt_bytes(const smc_model *m, int64_t P, int64_t t);
+smc_status smc_loglik_ckpt(const smc_model *m, int64_t P, const double *theta, int64_t t,
+                           double *loglik, void *ckpt, size_t ckpt_bytes, void *stream);
+smc_status smc_loglik_backward_ckpt(const smc_model *m, int64_t P, const double *theta, int64_t t,
+                                    const double *dloglik, double *dtheta, const void *ckpt,
+                                    size_t ckpt_bytes, void *stream);
+
 /* grad[i][p] = d/dtheta_i [log p(theta_p) + log p(y_{1:t} | theta_p)] for every
  * particle (pop->grad must be set; uses the workspace tail for checkpoints,
  * see smc_mala_workspace_bytes).  The Langevin kernel needs it at each new

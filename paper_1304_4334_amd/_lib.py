@@ -123,6 +123,13 @@ def lib():
         L.smc_loglik_backward.restype = st
         L.smc_loglik_backward.argtypes = [_vp, C.c_int64, _vp, C.c_int64, _vp, _vp, _vp,
                                           C.c_size_t, _vp]
+        L.smc_loglik_ckpt_bytes.restype = C.c_size_t
+        L.smc_loglik_ckpt_bytes.argtypes = [_vp, C.c_int64, C.c_int64]
+        L.smc_loglik_ckpt.restype = st
+        L.smc_loglik_ckpt.argtypes = [_vp, C.c_int64, _vp, C.c_int64, _vp, _vp, C.c_size_t, _vp]
+        L.smc_loglik_backward_ckpt.restype = st
+        L.smc_loglik_backward_ckpt.argtypes = [_vp, C.c_int64, _vp, C.c_int64, _vp, _vp, _vp,
+                                               C.c_size_t, _vp]
         L.smc_log_ml.restype = st
         L.smc_log_ml.argtypes = [C.c_int32, C.c_int32, _vp, _vp, _vp]
         L.smc_adapt_scale.restype = st
@@ -343,6 +350,28 @@ def smc_loglik_backward(model, theta, t, dloglik, stream=None):
     ws = torch.empty(max(nb, 1), dtype=torch.uint8, device=model.device)
     _check(lib().smc_loglik_backward(model.h, P, _ptr(theta), t, _ptr(dloglik), _ptr(dtheta),
                                      _ptr(ws), nb, _stream(stream)), "smc_loglik_backward")
+    return dtheta
+
+
+def smc_loglik_ckpt(model, theta, t, stream=None):
+    """smc_loglik that also leaves the adjoint's checkpoints: (loglik [P], a
+    uint8 tensor for smc_loglik_backward_ckpt)."""
+    P = int(theta.shape[1])
+    out = torch.empty(P, dtype=torch.float64, device=model.device)
+    nb = lib().smc_loglik_ckpt_bytes(model.h, P, t)
+    ckpt = torch.empty(nb, dtype=torch.uint8, device=model.device)
+    _check(lib().smc_loglik_ckpt(model.h, P, _ptr(theta), t, _ptr(out), _ptr(ckpt), nb,
+                                 _stream(stream)), "smc_loglik_ckpt")
+    return out, ckpt
+
+
+def smc_loglik_backward_ckpt(model, theta, t, dloglik, ckpt, stream=None):
+    """smc_loglik_backward from smc_loglik_ckpt's checkpoints."""
+    P = int(theta.shape[1])
+    dtheta = torch.empty_like(theta)
+    _check(lib().smc_loglik_backward_ckpt(model.h, P, _ptr(theta), t, _ptr(dloglik), _ptr(dtheta),
+                                          _ptr(ckpt), ckpt.numel(), _stream(stream)),
+           "smc_loglik_backward_ckpt")
     return dtheta
 
 

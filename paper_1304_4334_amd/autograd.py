@@ -1,5 +1,7 @@
-"""torch.autograd wrapper of the likelihood: forward smc_loglik, backward
-smc_loglik_backward (the hand-written adjoint).  Marshalling only."""
+"""torch.autograd wrapper of the likelihood: forward smc_loglik, or where a
+gradient may follow smc_loglik_ckpt, whose checkpoints are saved for the
+backward (smc_loglik_backward_ckpt, the hand-written adjoint), so that the
+recursion runs forward once.  Marshalling only."""
 from __future__ import annotations
 
 import torch
@@ -15,14 +17,17 @@ class SmcLoglik(torch.autograd.Function):
     def forward(ctx, theta, model, t):
         theta = theta.contiguous()
         ctx.model, ctx.t = model, t
-        ctx.save_for_backward(theta)
-        return _lib.smc_loglik(model, theta, t)
+        if not ctx.needs_input_grad[0]:
+            return _lib.smc_loglik(model, theta, t)
+        ll, ckpt = _lib.smc_loglik_ckpt(model, theta, t)
+        ctx.save_for_backward(theta, ckpt)
+        return ll
 
     @staticmethod
     def backward(ctx, grad_out):
-        (theta,) = ctx.saved_tensors
-        dtheta = _lib.smc_loglik_backward(ctx.model, theta, ctx.t,
-                                          grad_out.contiguous().to(torch.float64))
+        theta, ckpt = ctx.saved_tensors
+        dtheta = _lib.smc_loglik_backward_ckpt(ctx.model, theta, ctx.t,
+                                               grad_out.contiguous().to(torch.float64), ckpt)
         return dtheta, None, None
 
 

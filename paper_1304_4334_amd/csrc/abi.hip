@@ -708,6 +708,48 @@ smc_status smc_loglik_backward(const smc_model *m, int64_t P, const double *thet
   return launch_loglik_backward(m->dev, P, theta, t, dloglik, dtheta, ws, as_stream(stream));
 }
 
+size_t smc_loglik_ckpt_bytes(const smc_model *m, int64_t P, int64_t t) {
+  if (!m || P < 0 || t < 0) return 0;
+  return align256(adjoint_ckpt_bytes(m->dev, P, t)) + (size_t)P * sizeof(double);
+}
+
+smc_status smc_loglik_ckpt(const smc_model *m, int64_t P, const double *theta, int64_t t,
+                           double *loglik, void *ckpt, size_t ckpt_bytes, void *stream) {
+  smc_status st;
+  if ((st = check_model(m))) return st;
+  if (t < 0 || t > m->dev.T) return set_error(SMC_E_INVALID_ARG, "date t out of range");
+  if (P == 0) return SMC_OK;
+  if (P < 0 || !theta || !loglik) return set_error(SMC_E_INVALID_ARG, "bad loglik arguments");
+  const size_t need = smc_loglik_ckpt_bytes(m, P, t);
+  if (!ckpt || ckpt_bytes < need)
+    return set_error(SMC_E_WORKSPACE, "the checkpoints need %zu bytes", need);
+  if (reinterpret_cast<uintptr_t>(ckpt) & 7)
+    return set_error(SMC_E_INVALID_ARG, "the checkpoints are not 8-byte aligned");
+  double *se = reinterpret_cast<double *>(static_cast<char *>(ckpt) +
+                                          align256(adjoint_ckpt_bytes(m->dev, P, t)));
+  return launch_loglik_ckpt(m->dev, P, theta, t, loglik, se, ckpt, as_stream(stream));
+}
+
+smc_status smc_loglik_backward_ckpt(const smc_model *m, int64_t P, const double *theta, int64_t t,
+                                    const double *dloglik, double *dtheta, const void *ckpt,
+                                    size_t ckpt_bytes, void *stream) {
+  smc_status st;
+  if ((st = check_model(m))) return st;
+  if (t < 0 || t > m->dev.T) return set_error(SMC_E_INVALID_ARG, "date t out of range");
+  if (P == 0) return SMC_OK;
+  if (P < 0 || !theta || !dloglik || !dtheta)
+    return set_error(SMC_E_INVALID_ARG, "bad loglik_backward arguments");
+  const size_t need = smc_loglik_ckpt_bytes(m, P, t);
+  if (!ckpt || ckpt_bytes < need)
+    return set_error(SMC_E_WORKSPACE, "the checkpoints need %zu bytes", need);
+  if (reinterpret_cast<uintptr_t>(ckpt) & 7)
+    return set_error(SMC_E_INVALID_ARG, "the checkpoints are not 8-byte aligned");
+  void *c = const_cast<void *>(ckpt);  // only read
+  const double *se = reinterpret_cast<const double *>(
+      static_cast<const char *>(ckpt) + align256(adjoint_ckpt_bytes(m->dev, P, t)));
+  return launch_backward_from(m->dev, P, theta, t, dloglik, dtheta, c, se, as_stream(stream));
+}
+
 size_t smc_mala_workspace_bytes(const smc_model *m, int32_t J, int32_t N, int64_t max_chunk) {
   if (!m || J < 1 || N < 1) return 0;
   const size_t base = smc_workspace_bytes(m, J, N, max_chunk);

@@ -403,20 +403,41 @@ struct Adjoint<Egarch<K, SH, R, I>> {
     else return n * (p.cst - p.lsig) + kLn2 * sv - 0.5 * se;
   }
 
+  // The checkpoints through the likelihood's own forward recursion (advance(),
+  // advance_split()), and the density terms' sum, which FP64 Student-t
+  // gradients need (se).
+  struct Mark {
+    static constexpr bool on = true;
+    R *ckpt;
+    int64_t P, pidx;
+    bool live;
+    double se = 0.0;
+    __device__ __forceinline__ void operator()(int i, const typename Md::Run &r) {
+      if (i % SEG == 0 && live)
+#pragma unroll
+        for (int k = 0; k < K; ++k) ckpt[((int64_t)(i / SEG) * K + k) * P + pidx] = r.w[k];
+    }
+    __device__ __forceinline__ void done(double s) { se = s; }
+  };
+  static constexpr bool kNeedsSe = Md::kTLog;
+
   // Log-likelihood over 1..t from s0 and its gradient g[D] (accumulated into
   // g, times `scale`), one particle per lane.  ckpt: [nseg][K][P] of R; lds:
   // this lane's column base of a [SEG*K][64] buffer of R; st receives the
-  // state at t.
+  // state at t.  kFwd = false: the checkpoints are there (Mark), with their se;
+  // the gradient alone (0 is returned, st is not written).
+  template <bool kFwd = true>
   __device__ static double value_and_grad(const Par &p, const double *th, int64_t t,
                                           const Y *__restrict__ y, R *ckpt, int64_t P, int64_t pidx,
-                                          R *lds, double scale, double *g, R (&st)[Md::S]) {
+                                          R *lds, double scale, double *g, R (&st)[Md::S],
+                                          double se = 0.0) {
     if (t <= 0) {
 #pragma unroll
       for (int k = 0; k < Md::S; ++k) st[k] = (R)0;
       return 0.0;
     }
-    double se;
-    const double ll = forward(p, t, y, ckpt, P, pidx, true, nullptr, st, se);
+    double ll = 0.0;
+    if constexpr (kFwd) ll = forward(p, t, y, ckpt, P, pidx, true, nullptr, st, se);
     Sums<double> tot;
     Sums<R> sum;
     clear(tot);
@@ -531,11 +552,12 @@ struct Adjoint<Egarch<K, SH, R, I>> {
 
   // Called by all threads of a 512-thread block whose waves hold the same
   // particles (lanes that are not live repeat a live one and write nothing).
-  // The value, st and g are valid in wave 0.
+  // The value, st and g are valid in wave 0.  kFwd as for value_and_grad().
+  template <bool kFwd = true>
   __device__ static double block_value_and_grad(const Par &p, const double *th, int64_t t,
                                                 const Y *__restrict__ y, R *ckpt, int64_t P,
                                                 int64_t pidx, bool live, void *lds, double scale,
-                                                double *g, R (&st)[Md::S]) {
+                                                double *g, R (&st)[Md::S], double se = 0.0) {
     if (t <= 0) {
 #pragma unroll
       for (int k = 0; k < Md::S; ++k) st[k] = (R)0;
@@ -548,14 +570,6 @@ struct Adjoint<Egarch<K, SH, R, I>> {
     R *wring = ring + 3 * B * NF * 64;        // [2][B * K][64]
     constexpr int Q = SEG / B;                // sub-blocks of a segment
     const int ns = (int)nseg(t), nb = (int)((t + B - 1) / B);
-    double ll = 0.0, se = 0.0;
-    if (role == 0)
-      ll = forward(p, t, y, ckpt, P, pidx, live, wbuf + ((ns - 1) & 1) * SEG * K * 64, st, se);
-    lds_barrier();
-    Sums<double> tot;
-    Sums<R> sum;
-    clear(tot);
-    clear(sum);
     // Observations of sub-block b, one per lane (repeated; beyond t the last
     // one): loaded a stage ahead by a vector load, so that no wait for LDS
     // waits for them, and read lane by lane.
@@ -563,6 +577,39 @@ struct Adjoint<Egarch<K, SH, R, I>> {
       const int64_t s = (int64_t)b * B + (lane & (B - 1));
       return y[min(s, t - 1)];
     };
+    // Replays sub-block c of a segment into its buffer dst.
+    auto replay = [&](R *dst, int c, Y yv, typename Md::Run &r) {
+      R *d = dst + c * (B * K * 64);
+#pragma unroll
+      for (int u = 0; u < B; ++u) {
+#pragma unroll
+        for (int k = 0; k < K; ++k) d[(u * K + k) * 64] = r.w[k];
+        R ae = (R)0, pm = (R)1, Ed, zd;
+        (void)Md::step(p, lane_value(yv, u), r, ae, pm, Ed, zd);
+      }
+    };
+    const int top = nb - (ns - 1) * Q;  // sub-blocks of the last segment
+    double ll = 0.0;
+    if (role == 0) {
+      R *last = wbuf + ((ns - 1) & 1) * SEG * K * 64;
+      if constexpr (kFwd) {
+        ll = forward(p, t, y, ckpt, P, pidx, live, last, st, se);
+      } else {  // the last segment's exponents by a replay
+        typename Md::Run r;
+        load_ckpt(ckpt, ns - 1, P, pidx, r);
+        Y yv = fetch((ns - 1) * Q);
+        for (int c = 0; c < top; ++c) {
+          const Y yn = fetch(min((ns - 1) * Q + c + 1, nb - 1));
+          replay(last, c, yv, r);
+          yv = yn;
+        }
+      }
+    }
+    lds_barrier();
+    Sums<double> tot;
+    Sums<R> sum;
+    clear(tot);
+    clear(sum);
     auto count = [&](int b) { return b < nb - 1 ? B : (int)(t - (int64_t)b * B); };
     // f(u) for a sub-block's observations, last to first, unrolled when it is
     // whole
@@ -591,7 +638,6 @@ struct Adjoint<Egarch<K, SH, R, I>> {
       // buffer: a sub-block a stage; in FP32 from the second of sg's stages on
       // (chain() still reads sg + 1's exponents there in the first), two in
       // that one.  The last segment may have fewer stages than Q: then more.
-      const int top = nb - (ns - 1) * Q;  // stages of the last segment
       const int per = (Q + top - 1) / top;
       int k0 = 0;
       for (int i = 0; i < nb + 2; ++i) {
@@ -618,14 +664,7 @@ struct Adjoint<Egarch<K, SH, R, I>> {
                   ck[k] = ckpt[((int64_t)(sg - 2) * K + k) * P + pidx];
             }
             const Y yn = fetch(c + 1 < Q ? (sg - 1) * Q + c + 1 : max(sg - 2, 0) * Q);
-            R *d = dst + c * (B * K * 64);
-#pragma unroll
-            for (int u = 0; u < B; ++u) {
-#pragma unroll
-              for (int k = 0; k < K; ++k) d[(u * K + k) * 64] = r.w[k];
-              R ae = (R)0, pm = (R)1, Ed, zd;
-              (void)Md::step(p, lane_value(yv, u), r, ae, pm, Ed, zd);
-            }
+            replay(dst, c, yv, r);
             yv = yn;
           }
         }

@@ -1375,6 +1375,19 @@ smc_status launch_loglik_backward(const DevModel &m, int64_t P, const double *th
   return o ? o->loglik_backward(m, P, theta, t, dloglik, dtheta, ckpt, s) : SMC_E_UNSUPPORTED;
 }
 
+smc_status launch_loglik_ckpt(const DevModel &m, int64_t P, const double *theta, int64_t t,
+                              double *out, double *se, void *ckpt, hipStream_t s) {
+  const ModelOps *o = ops_for(m);
+  return o ? o->loglik_ckpt(m, P, theta, t, out, se, ckpt, s) : SMC_E_UNSUPPORTED;
+}
+
+smc_status launch_backward_from(const DevModel &m, int64_t P, const double *theta, int64_t t,
+                                const double *dloglik, double *dtheta, void *ckpt,
+                                const double *se, hipStream_t s) {
+  const ModelOps *o = ops_for(m);
+  return o ? o->backward_from(m, P, theta, t, dloglik, dtheta, ckpt, se, s) : SMC_E_UNSUPPORTED;
+}
+
 smc_status launch_grad_post(const DevModel &m, int64_t P, const double *theta, int64_t t,
                             double *grad, void *ckpt, hipStream_t s) {
   const ModelOps *o = ops_for(m);

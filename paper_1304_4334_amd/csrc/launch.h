@@ -80,6 +80,10 @@ struct ModelOps {
                              void *, const double *, const double *, uint64_t, uint64_t,
                              uint64_t, uint64_t, int64_t *, uint8_t *, const KernelTimer *,
                              hipStream_t);
+  smc_status (*loglik_ckpt)(const DevModel &, int64_t, const double *, int64_t, double *, double *,
+                            void *, hipStream_t);
+  smc_status (*backward_from)(const DevModel &, int64_t, const double *, int64_t, const double *,
+                              double *, void *, const double *, hipStream_t);
 };
 const ModelOps *ops_linreg(const DevModel &m);     // ops_linreg.hip
 const ModelOps *ops_egarch(const DevModel &m);     // ops_egarch.hip: Gaussian, Student-t
@@ -250,6 +254,13 @@ size_t adjoint_ckpt_bytes(const DevModel &m, int64_t P, int64_t t);
 smc_status launch_loglik_backward(const DevModel &m, int64_t P, const double *theta, int64_t t,
                                   const double *dloglik, double *dtheta, void *ckpt,
                                   hipStream_t s);
+// The likelihood that leaves the adjoint's checkpoints and the density terms'
+// sum se [P] (out may be NULL), and the gradient from them.
+smc_status launch_loglik_ckpt(const DevModel &m, int64_t P, const double *theta, int64_t t,
+                              double *out, double *se, void *ckpt, hipStream_t s);
+smc_status launch_backward_from(const DevModel &m, int64_t P, const double *theta, int64_t t,
+                                const double *dloglik, double *dtheta, void *ckpt,
+                                const double *se, hipStream_t s);
 smc_status launch_grad_post(const DevModel &m, int64_t P, const double *theta, int64_t t,
                             double *grad, void *ckpt, hipStream_t s);
 smc_status launch_mutate_mala(const DevModel &m, int64_t P, int64_t t, double *theta,

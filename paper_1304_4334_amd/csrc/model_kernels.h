@@ -723,10 +723,40 @@ constexpr bool grad_blocks() {
 }
 constexpr int kGradThreads = 512;
 
-template <class M>
+// The likelihood that leaves the adjoint's checkpoints, and in se (when not
+// NULL) the density terms' sum; out may be NULL.  kSplit: by blocks of four
+// waves (Egarch::advance_split).
+template <class M, bool kSplit>
+__global__ void __launch_bounds__((kSplit ? split_threads<M, kSplit>() : 64))
+    k_loglik_ckpt(int64_t P, const double *theta, int64_t t, double *out, double *se, void *ckpt,
+                  const typename M::Y *__restrict__ ydata) {
+  extern __shared__ double lds_dyn[];
+  const int64_t p = blockIdx.x * 64ll + (threadIdx.x & 63);
+  const bool live = p < P;
+  const int64_t pc = live ? p : P - 1;
+  using R = typename M::R;
+  double th[M::D];
+#pragma unroll
+  for (int i = 0; i < M::D; ++i) th[i] = theta[i * P + pc];
+  R st[M::S];
+#pragma unroll
+  for (int k = 0; k < M::S; ++k) st[k] = (R)0;
+  typename Adjoint<M>::Mark mark{typed<R>(ckpt), P, pc, live};
+  double ll;
+  if constexpr (kSplit) ll = M::advance_split(M::params(th), st, 0, t, ydata, lds_dyn, mark);
+  else ll = M::template advance<kAcc>(M::params(th), st, 0, t, ydata, mark);
+  if (threadIdx.x >= 64 || !live) return;
+  if (out) out[p] = ll;
+  if (se) se[p] = mark.se;
+}
+
+// dtheta = dloglik times the gradient, from the checkpoints; kFwd: with a
+// forward sweep that takes them first (and knows its own se).
+template <class M, bool kFwd>
 __global__ void __launch_bounds__(kGradThreads)
     k_loglik_backward_blk(int64_t P, const double *theta, int64_t t, const double *dloglik,
-                          double *dtheta, void *ckpt, const typename M::Y *__restrict__ y) {
+                          double *dtheta, void *ckpt, const double *se,
+                          const typename M::Y *__restrict__ y) {
   extern __shared__ double lds_dyn[];
   const int64_t p = blockIdx.x * 64ll + (threadIdx.x & 63);
   const bool live = p < P;
@@ -738,7 +768,11 @@ __global__ void __launch_bounds__(kGradThreads)
     g[i] = 0.0;
   }
   typename M::R st[Eval<M>::SR];
-  (void)ll_and_grad_block<M>(y, th, t, ckpt, P, pc, live, lds_dyn, dloglik[pc], g, st);
+  const double s = se && threadIdx.x < 64 ? se[pc] : 0.0;
+  using A = Adjoint<M>;
+  (void)A::template block_value_and_grad<kFwd>(M::params(th), th, t, y,
+                                                typed<typename M::R>(ckpt), P, pc, live, lds_dyn,
+                                                dloglik[pc], g, st, s);
   if (threadIdx.x < 64 && live)
 #pragma unroll
     for (int i = 0; i < M::D; ++i) dtheta[i * P + p] = g[i];
@@ -763,10 +797,11 @@ __global__ void __launch_bounds__(kGradThreads)
     for (int i = 0; i < M::D; ++i) grad[i * P + p] = g[i];
 }
 
-template <class M>
+template <class M, bool kFwd>
 __global__ void __launch_bounds__(64) k_loglik_backward(DevModel dm, int64_t P, const double *theta,
                                                         int64_t t, const double *dloglik,
-                                                        double *dtheta, void *ckpt) {
+                                                        double *dtheta, void *ckpt,
+                                                        const double *se) {
   extern __shared__ double lds_dyn[];
   const int64_t p = blockIdx.x * 64ll + threadIdx.x;
   if (p >= P) return;
@@ -777,7 +812,16 @@ __global__ void __launch_bounds__(64) k_loglik_backward(DevModel dm, int64_t P, 
     g[i] = 0.0;
   }
   typename M::R st[Eval<M>::SR];
-  (void)ll_and_grad<M>(dm, th, t, ckpt, P, p, lds_dyn, dloglik[p], g, st);
+  if constexpr (IsLinreg<M>::value) {
+    (void)ckpt;
+    (void)se;
+    (void)ll_and_grad<M>(dm, th, t, nullptr, P, p, lds_dyn, dloglik[p], g, st);
+  } else {
+    using R = typename M::R;
+    (void)Adjoint<M>::template value_and_grad<kFwd>(
+        M::params(th), th, t, M::ydata(dm), typed<R>(ckpt), P, p,
+        reinterpret_cast<R *>(lds_dyn) + threadIdx.x, dloglik[p], g, st, se ? se[p] : 0.0);
+  }
 #pragma unroll
   for (int i = 0; i < M::D; ++i) dtheta[i * P + p] = g[i];
 }
@@ -1070,24 +1114,65 @@ struct OpsOf {
     }
   }
 
+  // The regression has no recursion to check-point: the plain likelihood.
+  static smc_status loglik_ckpt(const DevModel &m, int64_t P, const double *theta, int64_t t,
+                                double *out, double *se, void *ckpt, hipStream_t s) {
+    if constexpr (IsLinreg<M>::value) {
+      return out ? loglik(m, P, theta, t, out, nullptr, s) : SMC_OK;
+    } else {
+      const typename M::Y *yd = Eval<M>::host_y(m);
+      if (!Adjoint<M>::kNeedsSe) se = nullptr;
+      if constexpr (M::kSplitOk)
+        if (split_density(m, P)) {
+          hipLaunchKernelGGL((k_loglik_ckpt<M, true>), grid_for(P, 64), dim3(M::kSplitThreads),
+                             split_lds<M>(false), s, P, theta, t, out, se, ckpt, yd);
+          return launch_status("loglik_ckpt");
+        }
+      hipLaunchKernelGGL((k_loglik_ckpt<M, false>), grid_for(P, 64), dim3(64), 0, s, P, theta, t,
+                         out, se, ckpt, yd);
+      return launch_status("loglik_ckpt");
+    }
+  }
+
+  template <bool kFwd>
+  static smc_status launch_backward(const DevModel &m, int64_t P, const double *theta, int64_t t,
+                                    const double *dloglik, double *dtheta, void *ckpt,
+                                    const double *se, hipStream_t s) {
+    if constexpr (grad_blocks<M>()) {
+      if (P <= kGradBlockMaxP<M>) {
+        hipLaunchKernelGGL((k_loglik_backward_blk<M, kFwd>), grid_for(P, 64), dim3(kGradThreads),
+                           Adjoint<M>::kBlkLds, s, P, theta, t, dloglik, dtheta, ckpt, se,
+                           Eval<M>::host_y(m));
+        return launch_status("loglik_backward");
+      }
+    }
+    hipLaunchKernelGGL((k_loglik_backward<M, kFwd>), grid_for(P, 64), dim3(64), lds_bytes_of<M>(), s,
+                       m, P, theta, t, dloglik, dtheta, ckpt, se);
+    return launch_status("loglik_backward");
+  }
+
+  static smc_status backward_from(const DevModel &m, int64_t P, const double *theta, int64_t t,
+                                  const double *dloglik, double *dtheta, void *ckpt,
+                                  const double *se, hipStream_t s) {
+    return launch_backward<false>(m, P, theta, t, dloglik, dtheta, ckpt, se, s);
+  }
+
+  // The caller's workspace holds the checkpoints alone.  Where the gradient
+  // also needs the density terms' sum, one kernel runs forward and back; else
+  // the forward recursion is the likelihood's (faster for mixtures, whose
+  // density waves the one-kernel form lacks).
   static smc_status loglik_backward(const DevModel &m, int64_t P, const double *theta, int64_t t,
                                     const double *dloglik, double *dtheta, void *ckpt,
                                     hipStream_t s) {
-    if constexpr (!HasAdjoint<M>::value) {
-      return set_error(SMC_E_UNSUPPORTED, "no adjoint for normal-mixture shocks");
-    } else {
-      if constexpr (grad_blocks<M>()) {
-        if (P <= kGradBlockMaxP<M>) {
-          hipLaunchKernelGGL(k_loglik_backward_blk<M>, grid_for(P, 64), dim3(kGradThreads),
-                             Adjoint<M>::kBlkLds, s, P, theta, t, dloglik, dtheta, ckpt,
-                             Eval<M>::host_y(m));
-          return launch_status("loglik_backward");
-        }
+    if constexpr (!IsLinreg<M>::value) {
+      if constexpr (Adjoint<M>::kNeedsSe) {
+        return launch_backward<true>(m, P, theta, t, dloglik, dtheta, ckpt, nullptr, s);
+      } else {
+        const smc_status st = loglik_ckpt(m, P, theta, t, nullptr, nullptr, ckpt, s);
+        if (st) return st;
       }
-      hipLaunchKernelGGL(k_loglik_backward<M>, grid_for(P, 64), dim3(64), lds_bytes_of<M>(), s, m,
-                         P, theta, t, dloglik, dtheta, ckpt);
-      return launch_status("loglik_backward");
     }
+    return launch_backward<false>(m, P, theta, t, dloglik, dtheta, ckpt, nullptr, s);
   }
 
   static smc_status grad_post(const DevModel &m, int64_t P, const double *theta, int64_t t,
@@ -1150,7 +1235,8 @@ const ModelOps *ops_table() {
                           &OpsOf<M>::loglik,     &OpsOf<M>::ckpt_bytes,
                           &OpsOf<M>::loglik_backward, &OpsOf<M>::grad_post,
                           &OpsOf<M>::mutate_mala, &OpsOf<M>::num_tests,
-                          &OpsOf<M>::test_fns,   &OpsOf<M>::mutate_indep};
+                          &OpsOf<M>::test_fns,   &OpsOf<M>::mutate_indep,
+                          &OpsOf<M>::loglik_ckpt, &OpsOf<M>::backward_from};
   return &o;
 }
 

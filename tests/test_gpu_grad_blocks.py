@@ -9,6 +9,7 @@ import torch
 
 import oracle as O
 import paper_1304_4334_amd as S
+from paper_1304_4334_amd import autograd as A
 import synthdata as SD
 from tests.gpu_helpers import gpu_model, ora_model
 
@@ -45,6 +46,39 @@ def test_blocks_equal_single_waves(name, prec):
         assert torch.isfinite(g).all()
         assert torch.equal(g, g1[:, :P]), (t, (g - g1[:, :P]).abs().max().item())
         assert torch.equal(g1[:, :P], g1[:, -P:])
+        # the pair that keeps the checkpoints: smc_loglik's values, and the
+        # gradients (FP64 Student-t: another order of the density terms' sum, so
+        # 1e-13 of the largest entry, far above the 1e-16 of a reordered sum)
+        ll, ck = S.smc_loglik_ckpt(m, th, t)
+        ll1, ck1 = S.smc_loglik_ckpt(m, many, t)
+        assert torch.equal(ll, S.smc_loglik(m, th, t)) and torch.equal(ll, ll1[:P])
+        h = S.smc_loglik_backward_ckpt(m, th, t, wt, ck)
+        h1 = S.smc_loglik_backward_ckpt(m, many, t, wmany, ck1)
+        assert torch.equal(h, h1[:, :P])
+        assert (h - g).abs().max() <= 1e-13 * g.abs().max()
+        assert torch.equal(h, S.smc_loglik_backward_ckpt(m, th, t, wt, ck))
+
+
+def test_autograd_runs_forward_once_and_back_twice():
+    """The autograd function: values of smc_loglik with and without a gradient
+    wanted, the gradient of smc_loglik_backward (1e-13, see above), a graph kept
+    for a second backward, saved-tensor hooks passed by, the regression."""
+    for name in ("egarch2t", "linreg"):
+        m = gpu_model(SD.workload(name, T=120))
+        x = torch.from_numpy(SD.random_thetas(SD.workload(name, T=120), 70, 2, spread=0.05).T.copy())
+        x = x.cuda()
+        w = torch.linspace(0.5, 1.5, 70, dtype=torch.float64, device="cuda")
+        want = S.smc_loglik_backward(m, x, 120, w)
+        assert torch.equal(A.loglik(x, m, 120), S.smc_loglik(m, x, 120))
+        th = x.clone().requires_grad_(True)
+        seen = []
+        with torch.autograd.graph.saved_tensors_hooks(lambda v: (seen.append(1), v.cpu())[1],
+                                                      lambda v: v.cuda()):
+            ll = A.loglik(th, m, 120)
+        assert len(seen) == 2 and torch.equal(ll, S.smc_loglik(m, x, 120))
+        for _ in range(2):
+            (g,) = torch.autograd.grad(ll, th, w, retain_graph=True)
+            assert (g - want).abs().max() <= 1e-13 * want.abs().max()
 
 
 @pytest.mark.parametrize("prec", [S.SMC_FP64, S.SMC_FP32])
