@@ -131,8 +131,9 @@ smc_status smc_model_destroy(smc_model *m);
  * forms the proposal scale), and observations per load batch of the
  * likelihood loop, 4, 8 or 16 (0 = the defaults 64 and 8).  A shape changes only the speed: every shape gives
  * the same results to the bit.  Shapes other than the default exist for
- * EGARCH(1) with Gaussian shocks and EGARCH(2) with Student-t shocks
- * (SMC_E_UNSUPPORTED otherwise).  The handle is changed: call it before the
+ * EGARCH(1) with Gaussian shocks, EGARCH(2) with Student-t shocks and
+ * egarch_23 (SMC_E_UNSUPPORTED otherwise); up to 32,768 particles of mixtures
+ * and FP64 Student-t shocks take blocks of their own, whatever the shape.  The handle is changed: call it before the
  * model is in use on any stream.  tune.py chooses shapes by timing them. */
 smc_status smc_model_set_launch(smc_model *m, int32_t block, int32_t unroll);
 int32_t smc_model_dim(const smc_model *m);       /* d, or -1 for NULL */
@@ -453,19 +454,21 @@ typedef struct {
  * walk, or the Langevin step: then every population needs pop->grad and a
  * workspace of smc_mala_workspace_bytes), use EGARCH(1) Gaussian or EGARCH(2)
  * Student-t models and the deterministic R_l rule, and either all adapt or
- * all replay.  At every step of the batch, the M
- * iterations of all runs then in their M phase go to one persistent kernel
- * launch in which each block takes (run, block of particles) items, longest
- * date first, from a device counter until they are exhausted; their moments
- * go to one pair of launches; C-phase chunks of different runs share one
- * host synchronisation.  `waves` is the number of persistent waves (0 =
- * 2048).  FP32 random-walk batches take the launch shape set on their first
+ * all replay.  An adaptive batch runs in up to four lanes, each with a part
+ * of the runs (of similar cost per iteration) and a stream of its own, the
+ * first on `stream`; `stream` has all of them behind it when the call returns.
+ * A replay, and a batch with `timing`, runs in one lane.  At every step of a
+ * lane, the M iterations of its runs then in their M phase go to one
+ * persistent kernel launch in which each block takes (run, block of particles)
+ * items, longest date first, from a device counter until they are exhausted;
+ * their moments go to one pair of launches; the stopping decisions of their
+ * C-phase chunks are taken on the device, as in smc_run.  `waves` is the number
+ * of persistent waves of a launch (0 = 2048).  FP32 random-walk batches take the launch shape set on their first
  * model (smc_model_set_launch: particles per block and item, observations
  * per load batch); other batches use 64 and 8.  bws: device, >= smc_batch_ws_bytes(n), 256-byte aligned.  A replay
  * batch never synchronises the stream (capturable in a graph); an adaptive
- * one synchronises once per batch step that evaluates C-phase chunks, and
- * stops with SMC_E_NUMERIC at the first such readback after a run raised a
- * numerical flag.  timing may be NULL (when given, the call synchronises at
+ * one waits for each lane's decisions, and stops with SMC_E_NUMERIC at the
+ * first decision after a run raised a numerical flag.  timing may be NULL (when given, the call synchronises at
  * its end to read the events).  Each run's results equal those of smc_run
  * with the same arguments. */
 smc_status smc_run_batch(int32_t n, const smc_model *const *models, smc_particles *const *pops,

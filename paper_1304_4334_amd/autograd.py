@@ -32,4 +32,5 @@ class SmcLoglik(torch.autograd.Function):
 
 
 def loglik(theta, model, t):
-    return SmcLoglik.apply(theta, model, t)
+    # without a graph no gradient can follow: no checkpoints to leave
+    return SmcLoglik.apply(theta if torch.is_grad_enabled() else theta.detach(), model, t)

@@ -10,6 +10,7 @@
 #include <chrono>
 #include <vector>
 
+#include "batch.h"
 #include "common.h"
 #include "launch.h"
 #include "smc.h"
@@ -145,22 +146,22 @@ DecisionSlot *decision_slot() {
   return buf;
 }
 
-// The calling thread's page-locked readback area for batched C phases, at
-// least n doubles; grown (reallocated) on demand and kept for the life of
-// the process; NULL if it cannot be had.
-double *batch_readback(size_t n) {
-  thread_local double *buf = nullptr;
-  thread_local size_t cap = 0;
-  if (cap < n) {
-    if (buf) (void)hipHostFree(buf);
-    buf = nullptr;
-    cap = 0;
+// The same for the runs of a batch, kMaxBatch of them 64 bytes apart.
+DecisionSlot *batch_slot(int i) {
+  constexpr size_t kStride = 64;
+  thread_local char *buf = nullptr;
+  thread_local bool tried = false;
+  if (!tried) {
+    tried = true;
     void *p = nullptr;
-    if (hipHostMalloc(&p, n * sizeof(double), hipHostMallocDefault) != hipSuccess) return nullptr;
-    buf = static_cast<double *>(p);
-    cap = n;
+    const unsigned flags = hipHostMallocCoherent | hipHostMallocMapped | hipHostMallocPortable;
+    if (hipHostMalloc(&p, kMaxBatch * kStride, flags) == hipSuccess) {
+      buf = static_cast<char *>(p);
+      for (int k = 0; k < kMaxBatch; ++k)
+        *reinterpret_cast<DecisionSlot *>(buf + k * kStride) = DecisionSlot{};
+    }
   }
-  return buf;
+  return buf ? reinterpret_cast<DecisionSlot *>(buf + i * kStride) : nullptr;
 }
 
 // An event (no timing) of the calling thread for the current device, marking
@@ -177,6 +178,30 @@ smc_status readback_event(hipEvent_t *out) {
   }
   *out = ev[dev];
   return SMC_OK;
+}
+
+// Further streams of the calling thread for the current device, with an event
+// each: the lanes of an adaptive batch.  Kept for the life of the process.
+constexpr int kMaxLanes = 4;
+struct LaneStream {
+  hipStream_t s = nullptr;
+  hipEvent_t ev = nullptr;
+};
+smc_status lane_stream(int i, LaneStream *out) {
+  thread_local LaneStream lanes[16][kMaxLanes];
+  int dev = -1;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 16)
+    return set_error(SMC_E_DEVICE, "batch lanes: device %d not supported", dev);
+  LaneStream &x = lanes[dev][i];
+  if ((!x.s && hipStreamCreateWithFlags(&x.s, hipStreamNonBlocking) != hipSuccess) ||
+      (!x.ev && hipEventCreateWithFlags(&x.ev, hipEventDisableTiming) != hipSuccess))
+    return set_error(SMC_E_DEVICE, "creating a batch lane failed");
+  *out = x;
+  return SMC_OK;
+}
+// Work queued on `to` from now on waits for what `from` holds.
+bool stream_after(hipStream_t to, hipStream_t from, hipEvent_t ev) {
+  return hipEventRecord(ev, from) == hipSuccess && hipStreamWaitEvent(to, ev, 0) == hipSuccess;
 }
 
 // Waits until the slot holds this call's whole decision for the chunk
@@ -1400,7 +1425,6 @@ smc_status smc_run_hybrid(const smc_model *m, smc_particles *pop, const smc_run_
 }  // extern "C"
 
 // ------------------------------------------------------------ batched runs --
-#include "batch.h"
 
 extern "C" {
 
@@ -1515,7 +1539,8 @@ smc_status smc_run_batch(int32_t n, const smc_model *const *models, smc_particle
     int64_t t_new = 0;    // end of the C phase
     int64_t chunk = 16, last_len = 0;
     bool zero_first = true;
-    std::vector<int64_t> dates;
+    int64_t t1 = 0;       // end of the chunk that waits for its decision
+    uint32_t seq = 0;     // its sequence number
     int32_t l = 0, r = 0, R = 0;
     double rss = NAN;
     int64_t evals = 0, steps = 0;
@@ -1528,34 +1553,81 @@ smc_status smc_run_batch(int32_t n, const smc_model *const *models, smc_particle
         (st = smc_init_from_prior(models[i], pops[i], cfgs[i].rng, stream)))
       return st;
   }
-  // Pinned readback area of the adaptive C phases: per run, the RSS of the
-  // chunk's checked dates followed by the run's flags word (a replay reads nothing back, so
-  // it can be captured).  One area per host thread, grown on demand and kept.
-  constexpr size_t kRow = kMaxChunk + 1;  // doubles per run
-  double *host_rss = nullptr;
-  if (!replay && !(host_rss = batch_readback((size_t)n * kRow)))
-    return set_error(SMC_E_DEVICE, "pinned host buffer for the batch failed");
-  auto flags_of = [&](int i) -> int32_t * {
-    return reinterpret_cast<int32_t *>(host_rss + (size_t)i * kRow + kMaxChunk);
+  // Every C-phase chunk's stopping decision is taken on the device and reaches
+  // the host through the run's page-locked slot (a replay decides nothing, so
+  // it can be captured).
+  if (!replay && !batch_slot(0))
+    return set_error(SMC_E_DEVICE, "page-locked slots for the batch failed");
+  thread_local uint32_t slot_seq = 0;
+  // An adaptive batch runs in up to kMaxLanes lanes, each with a stream and a
+  // part of the runs.  A lane's M iteration lasts as long as its longest run's,
+  // and its C phases stand between its M iterations, so in one lane every run
+  // waited for the longest at every step; the runs are sorted by cost per
+  // iteration and neighbours share a lane.  The host goes from lane to lane and
+  // never waits for one while another can go on.  The first lane runs on the
+  // caller's stream (four lanes then use the device's four hardware queues);
+  // the others start behind it, and it has them behind it when the call
+  // returns, also with an error.  One lane alone: a replay (which may be
+  // captured) and a timed batch (whose launches must not overlap).  Eight runs
+  // of 4,096 to 32,768 particles, T = 1,454 to 4,000: 44 ms in one lane, 32 in
+  // four; 32 runs of 774,144 particles: 399 and 319 ms.
+  struct Lane {
+    LaneStream ls;
+    std::vector<int> runs, pend;  // its runs; those waiting for a decision
+    unsigned int *queue = nullptr;
+    bool done = false;
+    // the watch on a lane that waits
+    bool idle = false;
+    std::chrono::steady_clock::time_point next_poll{}, idle_since{};
   };
+  const int n_lanes = replay || timing ? 1 : std::min(n, (int32_t)kMaxLanes);
+  std::vector<Lane> lanes(n_lanes);
+  {
+    std::vector<int> order(n);
+    for (int i = 0; i < n; ++i) order[i] = i;
+    const auto cost = [&](int i) { return (double)models[i]->dev.T * models[i]->dev.K; };
+    std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return cost(x) > cost(y); });
+    for (int q = 0; q < n; ++q) lanes[(int64_t)q * n_lanes / n].runs.push_back(order[q]);
+    for (int g = 0; g < n_lanes; ++g) {
+      std::sort(lanes[g].runs.begin(), lanes[g].runs.end());
+      lanes[g].queue = queue + 16 * g;
+      lanes[g].ls.s = s;
+      if (g > 0 && (st = lane_stream(g, &lanes[g].ls))) return st;
+    }
+  }
+  struct Join {
+    hipStream_t s;
+    std::vector<Lane> &lanes;
+    ~Join() {
+      for (Lane &l : lanes)
+        if (l.ls.s != s) (void)stream_after(s, l.ls.s, l.ls.ev);
+    }
+  } join{s, lanes};
+  for (Lane &l : lanes)
+    if (l.ls.s != s && !stream_after(l.ls.s, s, l.ls.ev))
+      return set_error(SMC_E_DEVICE, "batch: ordering the streams failed");
   // per-launch timing of the persistent M step
   struct Timed {
     hipEvent_t a = nullptr, b = nullptr;
   };
   std::vector<Timed> timed;
 
-  auto end_c_phase = [&](int i) -> smc_status {
+  // After the run's C phase: the S phase (unless it is queued already, behind
+  // the device's decision), then the M phase begins.
+  auto end_c_phase = [&](int i, hipStream_t cs, bool resampled) -> smc_status {
     Run &u = run[i];
     const smc_model *m = models[i];
     smc_particles *pop = pops[i];
     const smc_run_config &c = cfgs[i];
     smc_status e;
-    if ((e = launch_group_logwbar(pop->logw, pop->J, pop->N,
-                                  recs[i].group_logwbar + (int64_t)u.l * c.J, s)))
+    if (!resampled &&
+        ((e = launch_group_logwbar(pop->logw, pop->J, pop->N,
+                                   recs[i].group_logwbar + (int64_t)u.l * c.J, cs)) ||
+         (e = smc_resample(m, pop, c.scheme, c.rng, u.l + 1, cs))))
       return e;
-    if ((e = smc_resample(m, pop, c.scheme, c.rng, u.l + 1, stream))) return e;
     // the Langevin drift needs the posterior gradient at the new date
-    if (mala && (e = smc_posterior_grad(m, pop, u.tc, stream))) return e;
+    if (mala && (e = smc_posterior_grad(m, pop, u.tc, cs))) return e;
+
     u.t_new = u.tc;
     u.last_len = u.t_new - u.t;
     u.R = c.replay ? recs[i].R[u.l] : (u.rss < c.D2 ? c.kappa * c.Rbar : c.Rbar);
@@ -1566,13 +1638,17 @@ smc_status smc_run_batch(int32_t n, const smc_model *const *models, smc_particle
     return SMC_OK;
   };
 
-  for (;;) {
-    bool all_done = true;
-    for (int i = 0; i < n; ++i) all_done = all_done && run[i].ph == kDone;
-    if (all_done) break;
-    std::vector<int> pend;
+  // One step of a lane: its runs' C-phase chunks, then one M iteration of every
+  // run in its M phase.
+  auto lane_step = [&](Lane &lane) -> smc_status {
+    const hipStream_t cs = lane.ls.s;
+    std::vector<int> &pend = lane.pend;
+    pend.clear();
+    lane.done = true;
+    for (int i : lane.runs) lane.done = lane.done && run[i].ph == kDone;
+    if (lane.done) return SMC_OK;
     // (a) C phases: start or continue a chunk
-    for (int i = 0; i < n; ++i) {
+    for (int i : lane.runs) {
       Run &u = run[i];
       const smc_run_config &c = cfgs[i];
       const smc_model *m = models[i];
@@ -1593,11 +1669,11 @@ smc_status smc_run_batch(int32_t n, const smc_model *const *models, smc_particle
         u.zero_first = true;
         if (c.replay) {
           if ((st = launch_ccommit(m->dev, P, pop->theta, pop->state, pop->logw, pop->loglik,
-                                   u.t, u.t_stop, true, s)))
+                                   u.t, u.t_stop, true, cs)))
             return st;
           u.evals += P * (u.t_stop - u.t);
           u.tc = u.t_stop;
-          if ((st = end_c_phase(i))) return st;
+          if ((st = end_c_phase(i, cs, false))) return st;
           continue;
         }
         const int64_t cap = chunk_capacity(m, pop);
@@ -1607,45 +1683,54 @@ smc_status smc_run_batch(int32_t n, const smc_model *const *models, smc_particle
       }
       if (u.ph == kCNext) {
         const int64_t t1 = std::min(u.tc + u.chunk, u.t_stop);
-        u.dates.clear();
-        for (int64_t q = u.tc + 1; q <= t1; ++q)
-          if (q % c.check_every == 0 || q == u.t_stop) u.dates.push_back(q);
-        const WsLayout L = ws_layout(m->dev, pop->J, pop->N);
-        if (u.dates.empty()) {
+        // checked dates in (tc, t1]: the multiples of check_every, and t_stop
+        const int64_t ce = c.check_every;
+        const int64_t nc = t1 / ce - u.tc / ce + ((t1 == u.t_stop && u.t_stop % ce != 0) ? 1 : 0);
+        if (nc == 0) {
           if ((st = launch_ccommit(m->dev, P, pop->theta, pop->state, pop->logw, pop->loglik,
-                                   u.tc, t1, u.zero_first, s)))
+                                   u.tc, t1, u.zero_first, cs)))
             return st;
           u.evals += P * (t1 - u.tc);
           u.zero_first = false;
           u.tc = t1;
           continue;
         }
-        if ((st = launch_cscan(m->dev, P, pop->theta, pop->state, pop->logw, u.tc, t1,
-                               c.check_every, u.t_stop, u.zero_first, ws_at<double>(pop, L.wcols),
-                               s)) ||
-            (st = launch_rss_scan(ws_at<double>(pop, L.wcols), P, (int64_t)u.dates.size(),
-                                  ws_at<double>(pop, L.rsscols), s)))
+        // as smc_run's chunk: the commit to the decided date and the S phase
+        // (which does nothing unless the phase ended) follow the decision
+        const WsLayout L = ws_layout(m->dev, pop->J, pop->N);
+        double *W = ws_at<double>(pop, L.wcols), *rsscols = ws_at<double>(pop, L.rsscols);
+        StopInfo *stop_dev = ws_at<StopInfo>(pop, L.small + kSmallStop);
+        int32_t *dflags = ws_at<int32_t>(pop, L.small + kSmallFlags);
+        u.t1 = t1;
+        u.seq = ++slot_seq;
+        if ((st = launch_cscan(m->dev, P, pop->theta, pop->state, pop->logw, u.tc, t1, ce, u.t_stop,
+                               u.zero_first, W, cs)) ||
+            (st = launch_rss_scan(W, P, nc, rsscols, cs)) ||
+            (st = launch_find_stop(rsscols, nc, u.tc, t1, ce, u.t_stop, c.D1, stop_dev, cs,
+                                   batch_slot(i), u.seq, dflags)) ||
+            (st = launch_ccommit(m->dev, P, pop->theta, pop->state, pop->logw, pop->loglik, u.tc,
+                                 t1, u.zero_first, cs, &stop_dev->t_commit)) ||
+            (st = launch_resample(pop->logw, pop->J, pop->N, c.scheme, c.rng.seed, c.rng.run,
+                                  (uint64_t)(u.l + 1), pop->ancestor, ws_at<double>(pop, L.cum),
+                                  dflags, m->dev.d, m->dev.S, state_bytes(m), pop->theta,
+                                  pop->logprior, pop->loglik, pop->state, pop->grad,
+                                  ws_at<double>(pop, L.gather), cs, &stop_dev->ends,
+                                  recs[i].group_logwbar + (int64_t)u.l * c.J)))
           return st;
-        if (hipMemcpyAsync(host_rss + (size_t)i * kRow, ws_at<double>(pop, L.rsscols),
-                           u.dates.size() * sizeof(double), hipMemcpyDeviceToHost,
-                           s) != hipSuccess ||
-            hipMemcpyAsync(flags_of(i), ws_at<int32_t>(pop, L.small + kSmallFlags),
-                           sizeof(int32_t), hipMemcpyDeviceToHost, s) != hipSuccess)
-          return set_error(SMC_E_DEVICE, "run %d: RSS readback failed", i);
         u.ph = kCPend;
         pend.push_back(i);
       }
     }
     // (b) one M iteration of every run in its M phase
     std::vector<int> act;
-    for (int i = 0; i < n; ++i)
+    for (int i : lane.runs)
       if (run[i].ph == kM) act.push_back(i);
     if (!act.empty()) {
       std::stable_sort(act.begin(), act.end(),
                        [&](int a, int b) { return run[a].t_new > run[b].t_new; });
       BatchArgs ba{};
       ba.runs = table;
-      ba.queue = queue;
+      ba.queue = lane.queue;
       ba.n_active = (int32_t)act.size();
       ba.target_permille = mala ? 574 : 250;
       ba.kernel = kernel;
@@ -1698,7 +1783,7 @@ smc_status smc_run_batch(int32_t n, const smc_model *const *models, smc_particle
         timing->evals[2 * k + 1] = e2;
         timing->launches = k + 1;
       }
-      if ((st = launch_batch_m(ba, !replay, family, waves > 0 ? waves : 2048, s,
+      if ((st = launch_batch_m(ba, !replay, family, waves > 0 ? waves : 2048, cs,
                                timed_launch ? &kt : nullptr, bshape, ushape)))
         return st;
       for (int i : act) {
@@ -1715,50 +1800,75 @@ smc_status smc_run_batch(int32_t n, const smc_model *const *models, smc_particle
         }
       }
     }
-    // (c) one synchronisation for every pending C-phase chunk
-    if (!pend.empty()) {
-      if (hipStreamSynchronize(s) != hipSuccess)
-        return set_error(SMC_E_DEVICE, "batch synchronisation failed");
-      for (int i : pend) {
-        Run &u = run[i];
-        const smc_run_config &c = cfgs[i];
-        const smc_model *m = models[i];
-        smc_particles *pop = pops[i];
-        const int64_t P = (int64_t)pop->J * pop->N;
-        const double *hr = host_rss + (size_t)i * kRow;
-        // a run whose S or M phase raised a numerical flag stops the batch
-        // at its next C-phase readback, as smc_run stops
-        if (*flags_of(i)) {
-          recs[i].L = u.l;
-          return set_error(SMC_E_NUMERIC, "run %d: numerical flags 0x%x in cycle %d", i,
-                           *flags_of(i), u.l);
+    return SMC_OK;
+  };
+  // (c) the decision of a pending chunk, once it has arrived
+  auto decide = [&](int i, const StopInfo &got, int32_t flags, hipStream_t cs) -> smc_status {
+    Run &u = run[i];
+    smc_particles *pop = pops[i];
+    const int64_t P = (int64_t)pop->J * pop->N;
+    // a run whose S or M phase raised a numerical flag stops the batch at its
+    // next C-phase decision, as smc_run stops
+    if (flags) {
+      recs[i].L = u.l;
+      return set_error(SMC_E_NUMERIC, "run %d: numerical flags 0x%x in cycle %d", i, flags, u.l);
+    }
+    u.evals += P * (got.t_commit - u.tc);
+    u.zero_first = false;
+    u.rss = got.rss;
+    u.tc = got.t_commit;
+    if (got.ends) return end_c_phase(i, cs, true);
+    u.chunk = std::min(2 * u.chunk, chunk_capacity(models[i], pop));
+    u.ph = kCNext;
+    return SMC_OK;
+  };
+  // Goes round the lanes until all are done.  With every lane waiting, the
+  // streams are polled each millisecond; a lane whose stream has completed gets
+  // 10 more ms for its decision to show before the wait fails (as smc_run's).
+  using clock = std::chrono::steady_clock;
+  for (bool all_done = false; !all_done;) {
+    all_done = true;
+    for (Lane &lane : lanes) {
+      if (lane.done) continue;
+      std::vector<int> &pend = lane.pend;
+      for (size_t q = 0; q < pend.size();) {
+        const int i = pend[q];
+        StopInfo got{};
+        int32_t flags = 0;
+        if (!read_decision(batch_slot(i), run[i].seq, run[i].tc, run[i].t1, &got, &flags)) {
+          ++q;
+          continue;
         }
-        const int64_t nc = (int64_t)u.dates.size();
-        int64_t stop_col = -1;
-        for (int64_t q = 0; q < nc; ++q)
-          if (hr[q] < c.D1) {
-            stop_col = q;
-            break;
+        pend.erase(pend.begin() + q);
+        lane.idle = false;
+        if ((st = decide(i, got, flags, lane.ls.s))) return st;
+      }
+      if (pend.empty()) {
+        if ((st = lane_step(lane))) return st;
+        lane.next_poll = clock::now() + std::chrono::milliseconds(1);
+      } else if (clock::now() >= lane.next_poll) {
+        const auto now = clock::now();
+        lane.next_poll = now + std::chrono::milliseconds(1);
+        if (!lane.idle) {
+          const hipError_t e = hipStreamQuery(lane.ls.s);
+          if (e == hipSuccess) {
+            lane.idle = true;
+            lane.idle_since = now;
+          } else if (e != hipErrorNotReady) {
+            return set_error(SMC_E_DEVICE, "batch: a stream failed: %s", hipGetErrorString(e));
+          } else {
+            (void)hipGetLastError();  // not an error of the next launch
           }
-        const int64_t t1 = u.dates.back() < u.t_stop ? std::min(u.tc + u.chunk, u.t_stop)
-                                                      : u.t_stop;
-        const int64_t t_commit = stop_col >= 0 ? u.dates[stop_col] : t1;
-        if ((st = launch_ccommit(m->dev, P, pop->theta, pop->state, pop->logw, pop->loglik,
-                                 u.tc, t_commit, u.zero_first, s)))
-          return st;
-        u.evals += P * (t_commit - u.tc);
-        u.zero_first = false;
-        u.rss = stop_col >= 0 ? hr[stop_col] : hr[nc - 1];
-        u.tc = t_commit;
-        if (stop_col >= 0 || u.tc >= u.t_stop) {
-          if ((st = end_c_phase(i))) return st;
-        } else {
-          u.chunk = std::min(2 * u.chunk, chunk_capacity(m, pop));
-          u.ph = kCNext;
+        } else if (now - lane.idle_since > std::chrono::milliseconds(10)) {
+          return set_error(SMC_E_DEVICE, "batch: a stop decision did not reach the host");
         }
       }
+      all_done = all_done && lane.done;
     }
   }
+  for (Lane &l : lanes)
+    if (l.ls.s != s && !stream_after(s, l.ls.s, l.ls.ev))
+      return set_error(SMC_E_DEVICE, "batch: ordering the streams failed");
   for (int i = 0; i < n; ++i) {
     recs[i].L = run[i].l;
     recs[i].evals = run[i].evals;

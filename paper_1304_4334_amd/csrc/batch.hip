@@ -47,6 +47,8 @@ __device__ __forceinline__ int owner(const BatchArgs &a, int32_t i, bool mom) {
 __global__ void __launch_bounds__(256) k_batch_mom_partial(BatchArgs a) {
   __shared__ double red[4][256];
   typedef double double4v __attribute__((ext_vector_type(4)));
+  // the M step's work counter, for the launch that follows
+  if (blockIdx.x == 0 && threadIdx.x == 0) *a.queue = 0u;
   const int ri = owner(a, (int32_t)blockIdx.x, true);
   const BatchDyn &dy = a.dyn[ri];
   const BatchStatic &st = a.runs[dy.idx];
@@ -83,22 +85,29 @@ __global__ void __launch_bounds__(256) k_batch_mom_partial(BatchArgs a) {
   st.part[lb * 256 + tid] = (red[0][tid] + red[1][tid]) + (red[2][tid] + red[3][tid]);
 }
 
-__global__ void __launch_bounds__(256) k_batch_mom_final(BatchArgs a) {
-  __shared__ double Ms[256];
+// One block of 1,024 threads per run.  Bound by latency: the partials' loads
+// (each quarter of them by a quarter of the block, all in flight together; by
+// 256 threads in turn they took half of 12 us) and the factorisation.
+__global__ void __launch_bounds__(1024) k_batch_mom_final(BatchArgs a) {
+  __shared__ double Ms[256], quarter[4][256];
   __shared__ double Ls[16 * chol_ld<16>()];
   __shared__ double sh_h;
   const BatchDyn &dy = a.dyn[blockIdx.x];
   const BatchStatic &st = a.runs[dy.idx];
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x & 255, w = threadIdx.x >> 8;
   const int d = st.d;
   const int64_t P = st.P;
+  int32_t m0 = 0;
+  int64_t nacc = 0;
+  if (threadIdx.x == 0) {
+    m0 = *st.mh;
+    if (dy.mh_reset <= 0 && dy.prev_nacc) nacc = *dy.prev_nacc;
+  }
   // the partials added as k_mom_sum adds them: four quarters in block order,
   // then the quarters in order; each quarter's loads issued 32 at a time
   const int nb = dy.mom_nb, per = (nb + 3) / 4;
   constexpr int kBatch = 32;
-  double q[4];
-#pragma unroll
-  for (int w = 0; w < 4; ++w) {
+  {
     const int lo = min(nb, w * per), hi = min(nb, lo + per);
     double s = 0.0;
     for (int b0 = lo; b0 < hi; b0 += kBatch) {
@@ -109,15 +118,16 @@ __global__ void __launch_bounds__(256) k_batch_mom_final(BatchArgs a) {
       for (int u = 0; u < kBatch; ++u)
         if (b0 + u < hi) s += x[u];
     }
-    q[w] = s;
+    quarter[w][tid] = s;
   }
-  Ms[tid] = ((q[0] + q[1]) + q[2]) + q[3];
-  if (tid == 0) {
-    int32_t m = *st.mh;
+  __syncthreads();
+  if (w == 0) Ms[tid] = ((quarter[0][tid] + quarter[1][tid]) + quarter[2][tid]) + quarter[3][tid];
+  if (threadIdx.x == 0) {
+    int32_t m = m0;
     if (dy.mh_reset > 0) {
       m = dy.mh_reset;
     } else if (dy.prev_nacc) {
-      m += ((*dy.prev_nacc) * 1000 > (int64_t)a.target_permille * P) ? 1 : -1;
+      m += (nacc * 1000 > (int64_t)a.target_permille * P) ? 1 : -1;
       m = m < 1 ? 1 : (m > 10 ? 10 : m);
     }
     *st.mh = m;
@@ -130,9 +140,9 @@ __global__ void __launch_bounds__(256) k_batch_mom_final(BatchArgs a) {
   if (r < d && c < d)
     v = (Ms[r * 16 + c] - Ms[r * 16 + d] * Ms[c * 16 + d] * invP) / (double)(P - 1);
   __syncthreads();
-  if (r < d && c < d) Ms[r * 16 + c] = v;
+  if (w == 0 && r < d && c < d) Ms[r * 16 + c] = v;
   __syncthreads();
-  if (tid < 64) wave_cholesky<16>(Ms, Ls, d, sh_h, dy.hchol, st.flags);
+  if (threadIdx.x < 64) wave_cholesky<16>(Ms, Ls, d, sh_h, dy.hchol, st.flags);
 }
 
 // The random-walk M step of one particle of run `st` (as k_mutate_rw).
@@ -250,11 +260,12 @@ smc_status launch_batch_m(const BatchArgs &a, bool moments, int32_t family, int3
   if (moments) {
     hipLaunchKernelGGL(k_batch_mom_partial, grid_of(a.n_mom_items), dim3(256), 0, s, a);
     if ((st = launch_ok("batch/moments partial"))) return st;
-    hipLaunchKernelGGL(k_batch_mom_final, grid_of(a.n_active), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(k_batch_mom_final, grid_of(a.n_active), dim3(1024), 0, s, a);
     if ((st = launch_ok("batch/moments final"))) return st;
+  } else {  // a replay: no moments launch to clear the work counter
+    hipLaunchKernelGGL(k_batch_queue_reset, dim3(1), dim3(64), 0, s, a.queue);
+    if ((st = launch_ok("batch/queue reset"))) return st;
   }
-  hipLaunchKernelGGL(k_batch_queue_reset, dim3(1), dim3(64), 0, s, a.queue);
-  if ((st = launch_ok("batch/queue reset"))) return st;
   // `waves` persistent waves, in blocks of `block` threads
   const int32_t B = block ? block : 64;
   const int64_t blocks =
