@@ -999,7 +999,7 @@ smc_status smc_run(const smc_model *m, smc_particles *pop, const smc_run_config 
         ma.mean_out = mslot;
         if (fold) {
           int64_t nb = 0;
-          if ((st = launch_moment_partials(ma, &fm.part, nb, s))) return st;
+          if ((st = launch_moment_partials(dm, ma, &fm.part, nb, s))) return st;
           // two step-size slots, alternating, as every block reads the
           // previous iteration's value while block 0 writes this one's
           fm.nb = (int32_t)nb;
@@ -1219,7 +1219,7 @@ smc_status run_device_driven(const smc_model *m, smc_particles *pop, const smc_r
         ma.acc = dm.acc;  // the moment partials add the previous slot's accept counts
         MomFuse fm{};
         int64_t nb = 0;
-        if ((e = launch_moment_partials(ma, &fm.part, nb, cs))) return e;
+        if ((e = launch_moment_partials(dm, ma, &fm.part, nb, cs))) return e;
         fm.nb = (int32_t)nb;
         fm.target_permille = 250;
         fm.mh_out = mh;  // the kernel picks the slot pair and rule for its iteration

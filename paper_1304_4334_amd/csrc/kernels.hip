@@ -1581,8 +1581,20 @@ smc_status launch_moments(const MomArgs &a, hipStream_t s) {
   return launch_status("particle_moments/final");
 }
 
-smc_status launch_moment_partials(const MomArgs &a, const double **part, int64_t &nb,
-                                  hipStream_t s) {
+// Up to this many partials (4,096 particles) the step's blocks add them
+// themselves instead of reading k_mom_sum's sum: an adaptive run, launch of
+// the sum -> sum in the step, linreg T = 200: 1,024 particles 3,810 -> 3,370 us,
+// 4,096 3,830 -> 3,560, 8,192 (64 partials) 3,860 -> 3,900, 16,384 4,000 ->
+// 4,770; EGARCH(1,1) T = 1,000: 1,024 4,260 -> 3,960, 4,096 4,210 -> 4,030,
+// 8,192 4,460 -> 4,520.  Each block waits for its own loads, and there are
+// more of both as the population grows.  A step in blocks of 256 reads one
+// matrix at any size: its scaling wave is the block's critical path, and the
+// code that adds partials made a step of 65,536 EGARCH(2)-t particles 1.7 us
+// slower where it was only skipped.
+constexpr int64_t kMomDirect = 32;
+
+smc_status launch_moment_partials(const DevModel &m, const MomArgs &a, const double **part,
+                                  int64_t &nb, hipStream_t s) {
   if (a.d + 1 > kDMax) return set_error(SMC_E_UNSUPPORTED, "moments need d < %d", kDMax);
   int64_t chunk = 0;
   moment_partition(a.P, a.d, chunk, nb);
@@ -1598,6 +1610,8 @@ smc_status launch_moment_partials(const MomArgs &a, const double **part, int64_t
                        a.P, a.d, chunk, a.part, a.cyc, a.slot, a.acc);
   smc_status st = launch_status("particle_moments/partial");
   if (st) return st;
+  *part = a.part;
+  if (nb <= kMomDirect && (m.block != 256 || split_density(m, a.P))) return SMC_OK;
   // summed into the slot after the partials, as launch_moments does
   double *sums = a.part + nb * n;
   hipLaunchKernelGGL(k_mom_sum, dim3(n / 64), dim3(256), 0, s, a.part, (int32_t)nb, n, sums,

@@ -172,11 +172,12 @@ struct MomArgs {
                             // previous step's pending accept counts (acc_flush)
 };
 smc_status launch_moments(const MomArgs &a, hipStream_t s);
-// Only the partial sums of launch_moments, for a step that folds the rest in
-// (MomFuse): *part and nb receive the partials to add (for d >= 16 they are
-// first summed into one).
-smc_status launch_moment_partials(const MomArgs &a, const double **part, int64_t &nb,
-                                  hipStream_t s);
+// Only the partial sums of launch_moments, for a step of m that folds the rest
+// in (MomFuse): *part and nb receive the partials to add, or the one matrix
+// that they are summed into (beyond 32 of them, or where the step's blocks
+// have a scaling wave).
+smc_status launch_moment_partials(const DevModel &m, const MomArgs &a, const double **part,
+                                  int64_t &nb, hipStream_t s);
 // Particles per wave (chunk) and blocks (nb <= kMomBlocks) of the moment
 // partials of P particles of dimension d.
 void moment_partition(int64_t P, int32_t d, int64_t &chunk, int64_t &nb);

@@ -230,7 +230,7 @@ __global__ void __launch_bounds__(64) k_ccommit(DevModel dm, int64_t P, const do
 // ------------------------------------------------------------ M phase (a5) --
 // The proposal scale of a random-walk step computed by one wave of the
 // step's own block, its scaling wave or its first particle wave (MomFuse):
-// the moment partials summed entry by entry in block order, the step-size
+// the moment partials summed entry by entry as k_mom_sum does, the step-size
 // rule, V and its Cholesky factor in LDS, exactly as the separate moments
 // kernels do (k_mom_final).  Returns whether V was positive definite; h
 // receives the step size.  The wave orders its LDS accesses by wavefront
@@ -264,7 +264,7 @@ __device__ __forceinline__ void fused_scale_issue(const MomFuse &fm, ScalePre<D>
   }
 }
 
-template <int D, int W>
+template <int D, int W, bool kOne>
 __device__ __forceinline__ bool fused_scale(const MomFuse &fm, int64_t P, double *Ms, double *Ls,
                                             double *sh_h, double &h, const ScalePre<D> &pre) {
   const auto sync = [] { __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront"); };
@@ -272,14 +272,20 @@ __device__ __forceinline__ bool fused_scale(const MomFuse &fm, int64_t P, double
   const int lane = threadIdx.x & 63;
   int32_t m = pre.m;
   const int64_t nacc = pre.nacc;
-  // Lane entries idx = lane + 64 q, added in block order; the first partial
-  // came with pre, the rest (none when the partials come pre-summed into one
-  // matrix) in batches whose loads are all issued before any is added.
+  // Lane entries idx = lane + 64 q; the first matrix came with pre.  It is
+  // the only one (always where kOne), or the other partials are loaded in
+  // batches, each issued before any of it is added, and added as k_mom_sum
+  // does: quarters in block order, then the quarters in order.
   constexpr int Q = ScalePre<D>::Q;
   constexpr int kB = Q >= 32 ? 1 : 32 / Q;  // partials per entry in flight
-  double sum[Q];
+  const int per = (fm.nb + 3) / 4;
+  int end = per;
+  double sum[Q], tot[Q];
 #pragma unroll
-  for (int q = 0; q < Q; ++q) sum[q] = 0.0 + pre.x0[q];
+  for (int q = 0; q < Q; ++q) {
+    sum[q] = 0.0 + pre.x0[q];
+    tot[q] = 0.0;
+  }
   for (int b0 = 1; b0 < fm.nb; b0 += kB) {
     double x[Q][kB];
 #pragma unroll
@@ -290,16 +296,34 @@ __device__ __forceinline__ bool fused_scale(const MomFuse &fm, int64_t P, double
       for (int u = 0; u < kB; ++u)
         x[q][u] = (idx < E && b0 + u < fm.nb) ? fm.part[(int64_t)(b0 + u) * W * W + e] : 0.0;
     }
+    if constexpr (kOne) {
 #pragma unroll
-    for (int q = 0; q < Q; ++q)
+      for (int q = 0; q < Q; ++q)
 #pragma unroll
-      for (int u = 0; u < kB; ++u)
-        if (b0 + u < fm.nb) sum[q] += x[q][u];
+        for (int u = 0; u < kB; ++u)
+          if (b0 + u < fm.nb) sum[q] += x[q][u];
+      continue;
+    }
+#pragma unroll
+    for (int u = 0; u < kB; ++u) {
+      if (b0 + u >= fm.nb) break;
+      if (b0 + u == end) {
+        end += per;
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+          tot[q] += sum[q];
+          sum[q] = 0.0;
+        }
+      }
+#pragma unroll
+      for (int q = 0; q < Q; ++q) sum[q] += x[q][u];
+    }
   }
 #pragma unroll
   for (int q = 0; q < Q; ++q) {
     const int idx = lane + 64 * q;
-    if (idx < E) Ms[(idx / (D + 1)) * W + idx % (D + 1)] = sum[q];
+    if (idx < E)
+      Ms[(idx / (D + 1)) * W + idx % (D + 1)] = kOne ? sum[q] : tot[q] + sum[q];
   }
   if (lane == 0) {
     if (fm.mh_reset > 0) {
@@ -402,7 +426,7 @@ __global__ void __launch_bounds__((rw_threads<M, B, kSplit>())) k_mutate_rw(DevM
       ScalePre<D> pre;
       fused_scale_issue<D, W>(fm, pre);
       double hs = 0.0;
-      const bool ok = fused_scale<D, W>(fm, P, Ms, Ls, &sh_h, hs, pre);
+      const bool ok = fused_scale<D, W, kScaleWave>(fm, P, Ms, Ls, &sh_h, hs, pre);
       if (threadIdx.x == B) sh_ok = ok;
       __syncthreads();
       return;
@@ -442,7 +466,7 @@ __global__ void __launch_bounds__((rw_threads<M, B, kSplit>())) k_mutate_rw(DevM
       if constexpr (!kScaleWave) {
         if (threadIdx.x < 64) {
           double hs = 0.0;
-          const bool ok = fused_scale<D, W>(fm, P, Ms, Ls, &sh_h, hs, pre);
+          const bool ok = fused_scale<D, W, kScaleWave>(fm, P, Ms, Ls, &sh_h, hs, pre);
           if (threadIdx.x == 0) sh_ok = ok;
         }
       }
