@@ -239,28 +239,17 @@ __global__ void __launch_bounds__(256) k_rss_scan(const double *trip, int64_t P,
   }
 }
 
-// The chunk's stopping decision (Section 3.3: the first checked date whose
-// RSS is below rss_min): one wave scans the RSS values 64 at a time.  Value c
-// is that of date first + c * check_every, the multiples of check_every after
-// t up to t1, and t_max last when it is not a multiple.  With host_slot, the
-// decision and the flags word also go to host memory, every 32-bit word of
-// them paired with seq in an 8-byte word (DecisionSlot).  With cyc (a
-// device-driven chunk) the chunk comes from there, a chunk without checked
-// dates commits to t1 and does not end the phase, and the decision opens the
-// S and M phases of a phase that ended: R = kappa Rbar iterations when the
-// RSS is below D2, else Rbar (Section 3.3).
-__global__ void __launch_bounds__(64) k_find_stop(const double *rss, int32_t nc, int64_t t,
-                                                  int64_t t1, int64_t check_every, int64_t t_max,
-                                                  double rss_min, StopInfo *out,
-                                                  DecisionSlot *host_slot, uint32_t seq,
-                                                  const int32_t *flags, CycleDyn *cyc) {
-  if (cyc) {
-    if (!cyc->go_c) return;
-    nc = cyc->nc;
-    t = cyc->t;
-    t1 = cyc->t1;
-    t_max = cyc->t_stop;
-  }
+// A device-driven chunk's stopping decision (decide_stop): one wave scans the
+// RSS values 64 at a time.  A chunk without checked dates commits to t1 and
+// does not end the phase, and the decision opens the S and M phases of a phase
+// that ended: R = kappa Rbar iterations when the RSS is below D2, else Rbar
+// (Section 3.3).  Chunks that the host opens are decided in the commit's
+// launch; here the commit's blocks read the fields that this kernel writes.
+__global__ void __launch_bounds__(64) k_find_stop(const double *rss, int64_t check_every,
+                                                  double rss_min, StopInfo *out, CycleDyn *cyc) {
+  if (!cyc->go_c) return;
+  const int32_t nc = cyc->nc;
+  const int64_t t = cyc->t, t1 = cyc->t1, t_max = cyc->t_stop;
   int first = -1;
   for (int base = 0; base < nc; base += 64) {
     const int c = base + (int)threadIdx.x;
@@ -271,33 +260,19 @@ __global__ void __launch_bounds__(64) k_find_stop(const double *rss, int32_t nc,
     }
   }
   if (threadIdx.x == 0) {
-    const int64_t first_date = (t / check_every + 1) * check_every;
-    const int64_t n_regular = t1 >= first_date ? (t1 - first_date) / check_every + 1 : 0;
-    const int col = first >= 0 ? first : nc - 1;
     StopInfo o;
-    o.t_commit = first < 0 ? t1 : (first < n_regular ? first_date + first * check_every : t_max);
-    o.rss = nc > 0 ? rss[col] : (cyc ? cyc->rss : 1.0);
+    o.t_commit = stop_date(first, t, t1, check_every, t_max);
+    o.rss = nc > 0 ? rss[first >= 0 ? first : nc - 1] : cyc->rss;
     o.below = first >= 0;
     o.ends = nc > 0 && (first >= 0 || t1 >= t_max);
     *out = o;
-    if (cyc) {
-      const int32_t R = o.ends ? (o.rss < cyc->D2 ? cyc->kR : cyc->Rbar) : 0;
-      cyc->t_new = o.t_commit;
-      cyc->rss = o.rss;
-      cyc->R = R;
-      cyc->r0 = 0;
-      cyc->go_s = o.ends;
-      cyc->go_m = o.ends;
-    }
-    if (host_slot) {
-      const int32_t fl = *flags;
-      const uint64_t tc = (uint64_t)o.t_commit;
-      const uint64_t rb = __builtin_bit_cast(uint64_t, o.rss);
-      uint4 *dst = reinterpret_cast<uint4 *>(host_slot);
-      dst[0] = make_uint4(seq, (uint32_t)tc, seq, (uint32_t)(tc >> 32));
-      dst[1] = make_uint4(seq, (uint32_t)rb, seq, (uint32_t)(rb >> 32));
-      dst[2] = make_uint4(seq, (uint32_t)fl, seq, (uint32_t)(o.ends | (o.below << 1)));
-    }
+    const int32_t R = o.ends ? (o.rss < cyc->D2 ? cyc->kR : cyc->Rbar) : 0;
+    cyc->t_new = o.t_commit;
+    cyc->rss = o.rss;
+    cyc->R = R;
+    cyc->r0 = 0;
+    cyc->go_s = o.ends;
+    cyc->go_m = o.ends;
   }
 }
 
@@ -529,9 +504,11 @@ __device__ __forceinline__ void group_max_sum(const double *lw, int32_t N, doubl
   mx = m;
 }
 
-// log wbar_j = log(N^-1 sum_n exp(logw_jn)) per group (Section 4.2).
+// log wbar_j = log(N^-1 sum_n exp(logw_jn)) per group (Section 4.2); with go,
+// only when *go is not 0.
 __global__ void __launch_bounds__(kSBlock) k_group_logwbar(const double *logw, int32_t N,
-                                                           double *out) {
+                                                           double *out, const int32_t *go) {
+  if (go && *go == 0) return;  // enqueued ahead of a C phase that did not end
   __shared__ double sh[kSWaves];
   double mx, s;
   group_max_sum(logw + (int64_t)blockIdx.x * N, N, nullptr, sh, mx, s);
@@ -1307,7 +1284,19 @@ smc_status launch_ccommit(const DevModel &m, int64_t P, const double *theta, voi
                           double *logw, double *loglik, int64_t t0, int64_t t1, bool zero_first,
                           hipStream_t s, const int64_t *t1_dev) {
   const ModelOps *o = ops_for(m);
-  return o ? o->ccommit(m, P, theta, state, logw, loglik, t0, t1, zero_first, t1_dev, s)
+  return o ? o->ccommit(m, P, theta, state, logw, loglik, t0, t1, zero_first, t1_dev, StopRule{},
+                        s)
+           : SMC_E_UNSUPPORTED;
+}
+
+smc_status launch_decide_commit(const DevModel &m, int64_t P, const double *theta, void *state,
+                                double *logw, double *loglik, bool zero_first,
+                                const StopRule &rule, hipStream_t s) {
+  if (rule.nc < 1 || rule.nc > kMaxChunk)
+    return set_error(SMC_E_INVALID_ARG, "stop search over %d columns", rule.nc);
+  const ModelOps *o = ops_for(m);
+  return o ? o->ccommit(m, P, theta, state, logw, loglik, rule.t, rule.t1, zero_first, nullptr,
+                        rule, s)
            : SMC_E_UNSUPPORTED;
 }
 
@@ -1463,14 +1452,9 @@ smc_status launch_rss_scan(const double *trip, int64_t P, int64_t ncols, double 
   return launch_status("correct/rss");
 }
 
-smc_status launch_find_stop(const double *rss, int64_t nc, int64_t t, int64_t t1,
-                            int64_t check_every, int64_t t_max, double rss_min, StopInfo *out,
-                            hipStream_t s, DecisionSlot *host_slot, uint32_t seq,
-                            const int32_t *flags, CycleDyn *cyc) {
-  if (!cyc && (nc < 1 || nc > kMaxChunk))
-    return set_error(SMC_E_INVALID_ARG, "stop search over %lld columns", (long long)nc);
-  hipLaunchKernelGGL(k_find_stop, dim3(1), dim3(64), 0, s, rss, (int32_t)nc, t, t1, check_every,
-                     t_max, rss_min, out, host_slot, seq, flags, cyc);
+smc_status launch_find_stop(const double *rss, int64_t check_every, double rss_min, StopInfo *out,
+                            CycleDyn *cyc, hipStream_t s) {
+  hipLaunchKernelGGL(k_find_stop, dim3(1), dim3(64), 0, s, rss, check_every, rss_min, out, cyc);
   return launch_status("correct/find_stop");
 }
 
@@ -1511,8 +1495,8 @@ smc_status launch_phase_out(const CycleDyn *c, const double *rss_src, int64_t t_
 }
 
 smc_status launch_group_logwbar(const double *logw, int32_t J, int32_t N, double *out,
-                                hipStream_t s) {
-  hipLaunchKernelGGL(k_group_logwbar, dim3(J), dim3(kSBlock), 0, s, logw, N, out);
+                                hipStream_t s, const int32_t *go) {
+  hipLaunchKernelGGL(k_group_logwbar, dim3(J), dim3(kSBlock), 0, s, logw, N, out, go);
   return launch_status("correct/group_logwbar");
 }
 

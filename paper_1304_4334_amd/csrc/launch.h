@@ -49,6 +49,31 @@ struct MomFuse {
   int32_t *flags;            // SMC_FLAG_NOT_PD when the variance is not positive definite
 };
 
+// A chunk's stopping decision (Section 3.3): its nc RSS values (0: none to be
+// made), the dates they belong to, and where the decision goes: to *out, and
+// with *flags into page-locked host memory slot (tagged with seq) when that is
+// not NULL.
+struct StopRule {
+  const double *rss;
+  int64_t t, t1, check_every, t_max;  // the chunk (t, t1] and the phase's last date
+  double rss_min;
+  StopInfo *out;
+  DecisionSlot *slot;
+  const int32_t *flags;
+  int32_t nc;
+  uint32_t seq;
+};
+
+// The date a chunk commits to: checked date `first` (dates are the multiples
+// of check_every after t up to t1, and t_max last when it is not a multiple),
+// or the chunk's end when no RSS was below (-1).
+__host__ __device__ __forceinline__ int64_t stop_date(int first, int64_t t, int64_t t1,
+                                                      int64_t check_every, int64_t t_max) {
+  const int64_t first_date = (t / check_every + 1) * check_every;
+  const int64_t n_regular = t1 >= first_date ? (t1 - first_date) / check_every + 1 : 0;
+  return first < 0 ? t1 : (first < n_regular ? first_date + first * check_every : t_max);
+}
+
 // Launchers of the kernels templated on the model, one table per model type
 // (model_kernels.h); the family tables below return NULL for a description
 // they do not cover.
@@ -58,7 +83,7 @@ struct ModelOps {
   smc_status (*cscan)(const DevModel &, int64_t, const double *, const void *, const double *,
                       int64_t, int64_t, int64_t, int64_t, bool, double *, hipStream_t);
   smc_status (*ccommit)(const DevModel &, int64_t, const double *, void *, double *, double *,
-                        int64_t, int64_t, bool, const int64_t *, hipStream_t);
+                        int64_t, int64_t, bool, const int64_t *, const StopRule &, hipStream_t);
   smc_status (*mutate_rw)(const DevModel &, int64_t, int64_t, double *, double *, double *,
                           void *, const double *, uint64_t, uint64_t, uint64_t, uint64_t,
                           int64_t *, uint8_t *, const KernelTimer *, const MomFuse *,
@@ -117,15 +142,15 @@ int64_t rss_slice_doubles(int64_t P);
 smc_status launch_rss_scan(const double *trip, int64_t P, int64_t ncols, double *rss,
                            hipStream_t s, const int32_t *ncols_dev = nullptr);
 smc_status launch_group_logwbar(const double *logw, int32_t J, int32_t N, double *out,
-                                hipStream_t s);
-// The stopping decision over the nc RSS values of the chunk (t, t1] into *out,
-// and with *flags into page-locked host memory host_slot (tagged with seq)
-// when that is not NULL; with cyc, the chunk and decision of a device-driven
-// cycle (the by-value chunk arguments are then unused).
-smc_status launch_find_stop(const double *rss, int64_t nc, int64_t t, int64_t t1,
-                            int64_t check_every, int64_t t_max, double rss_min, StopInfo *out,
-                            hipStream_t s, DecisionSlot *host_slot = nullptr, uint32_t seq = 0,
-                            const int32_t *flags = nullptr, CycleDyn *cyc = nullptr);
+                                hipStream_t s, const int32_t *go = nullptr);
+// A device-driven chunk's stopping decision over its RSS values (the chunk and
+// the decision's effects in *cyc).
+smc_status launch_find_stop(const double *rss, int64_t check_every, double rss_min, StopInfo *out,
+                            CycleDyn *cyc, hipStream_t s);
+// A chunk's stopping decision and the commit to the decided date.
+smc_status launch_decide_commit(const DevModel &m, int64_t P, const double *theta, void *state,
+                                double *logw, double *loglik, bool zero_first,
+                                const StopRule &rule, hipStream_t s);
 // Resampling and the replacement of every particle by its ancestor, one block
 // per group; with `go` (device flag, may be NULL) the kernel does nothing
 // while *go is 0; with group_logwbar (may be NULL) it also writes each

@@ -191,16 +191,59 @@ __global__ void __launch_bounds__(64) k_cscan(DevModel dm, int64_t P, const doub
   while (nrec > ndone) reduce(min(16, nrec - ndone));
 }
 
+// The first checked date of rule's chunk whose RSS is below rss_min, by a
+// whole wave: its column, or -1.  Eight loads of a lane are in flight.
+__device__ __forceinline__ int decide_stop(const StopRule &rule) {
+  for (int base = 0; base < rule.nc; base += 512) {
+    double x[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      x[u] = rule.rss[min(base + 64 * u + (int)threadIdx.x, rule.nc - 1)];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int c = base + 64 * u + (int)threadIdx.x;
+      const uint64_t below = __ballot(c < rule.nc && x[u] < rule.rss_min);
+      if (below) return base + 64 * u + __builtin_ctzll(below);
+    }
+  }
+  return -1;
+}
+
 // Commit: advance from t0 to t1 (or to *t1_dev when given), adding the log
 // densities to logw and loglik.  A device-driven chunk takes t0, t1 and
-// zero_first from dm.cyc.
+// zero_first from dm.cyc.  With rule.nc, every wave first makes the chunk's
+// stopping decision for itself and commits to its date, and the first one
+// hands it to the S phase and the host: a kernel of its own for one wave's
+// work took 1.8 us and a launch gap of about 2 in each of a run's C phases.
 template <class M>
 __global__ void __launch_bounds__(64) k_ccommit(DevModel dm, int64_t P, const double *theta,
                                                 void *state, double *logw, double *loglik,
                                                 int64_t t0, int64_t t1, int32_t zero_first,
-                                                const int64_t *t1_dev,
+                                                const int64_t *t1_dev, StopRule rule,
                                                 const typename M::Y *__restrict__ ydata) {
   const int64_t p = blockIdx.x * 64ll + threadIdx.x;
+  if (rule.nc) {  // by all the wave's lanes, those past P too
+    const int first = decide_stop(rule);
+    t1 = stop_date(first, rule.t, rule.t1, rule.check_every, rule.t_max);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+      StopInfo o;
+      o.t_commit = t1;
+      o.rss = rule.rss[first >= 0 ? first : rule.nc - 1];
+      o.below = first >= 0;
+      o.ends = first >= 0 || rule.t1 >= rule.t_max;
+      *rule.out = o;
+      if (rule.slot) {
+        const uint32_t seq = rule.seq;
+        const int32_t fl = *rule.flags;
+        const uint64_t tc = (uint64_t)o.t_commit;
+        const uint64_t rb = __builtin_bit_cast(uint64_t, o.rss);
+        uint4 *dst = reinterpret_cast<uint4 *>(rule.slot);
+        dst[0] = make_uint4(seq, (uint32_t)tc, seq, (uint32_t)(tc >> 32));
+        dst[1] = make_uint4(seq, (uint32_t)rb, seq, (uint32_t)(rb >> 32));
+        dst[2] = make_uint4(seq, (uint32_t)fl, seq, (uint32_t)(o.ends | (o.below << 1)));
+      }
+    }
+  }
   if (p >= P) return;
   if (const CycleDyn *c = dm.cyc) {
     if (!c->go_c) return;
@@ -1077,9 +1120,10 @@ struct OpsOf {
 
   static smc_status ccommit(const DevModel &m, int64_t P, const double *theta, void *state,
                             double *logw, double *loglik, int64_t t0, int64_t t1,
-                            bool zero_first, const int64_t *t1_dev, hipStream_t s) {
+                            bool zero_first, const int64_t *t1_dev, const StopRule &rule,
+                            hipStream_t s) {
     hipLaunchKernelGGL(k_ccommit<M>, grid_for(P, 64), dim3(64), 0, s, m, P, theta, state, logw,
-                       loglik, t0, t1, (int32_t)zero_first, t1_dev, Eval<M>::host_y(m));
+                       loglik, t0, t1, (int32_t)zero_first, t1_dev, rule, Eval<M>::host_y(m));
     return launch_status("correct/commit");
   }
 
