@@ -373,16 +373,15 @@ struct Adjoint<Egarch<K, SH, R, I>> {
           for (int u = 0; u < kFwd; ++u) {
             one(j + u, u, yb[u]);
             if constexpr (Md::kTLog) {
-              const R x = tx[u] = Md::t_x(p, lastz, lastE);
-              pm = u == 0 ? x : Md::t_join(pm, x);
-              if (u == kFwd - 1) ae += Md::t_group_log(pm, tx);
+              tx[u] = Md::t_x(p, lastz, lastE);
+              if (u == kFwd - 1) ae += Md::t_group_log(tx);
             }
           }
         }
       }
       for (; j < len; ++j) {
         one(j, j % kFwd, ys[j]);
-        if constexpr (Md::kTLog) ae += log1p_pos(Md::t_x(p, lastz, lastE));
+        if constexpr (Md::kTLog) ae += log1p_pos<true>(Md::t_x(p, lastz, lastE));
       }
       if constexpr (Md::kTProd) ae += log2_fast(pm);
       sv += (double)av;
