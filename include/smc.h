@@ -468,8 +468,9 @@ typedef struct {
  * per load batch); other batches use 64 and 8.  bws: device, >= smc_batch_ws_bytes(n), 256-byte aligned.  A replay
  * batch never synchronises the stream (capturable in a graph); an adaptive
  * one waits for each lane's decisions, and stops with SMC_E_NUMERIC at the
- * first decision after a run raised a numerical flag.  timing may be NULL (when given, the call synchronises at
- * its end to read the events).  Each run's results equal those of smc_run
+ * first decision after a run raised a numerical flag; with any error, all its
+ * work has completed when the call returns.  timing may be NULL (when given,
+ * the call synchronises at its end to read the events).  Each run's results equal those of smc_run
  * with the same arguments. */
 smc_status smc_run_batch(int32_t n, const smc_model *const *models, smc_particles *const *pops,
                          const smc_run_config *cfgs, smc_run_record *recs, void *bws,

@@ -1566,7 +1566,7 @@ smc_status smc_run_batch(int32_t n, const smc_model *const *models, smc_particle
   // never waits for one while another can go on.  The first lane runs on the
   // caller's stream (four lanes then use the device's four hardware queues);
   // the others start behind it, and it has them behind it when the call
-  // returns, also with an error.  One lane alone: a replay (which may be
+  // returns.  One lane alone: a replay (which may be
   // captured) and a timed batch (whose launches must not overlap).  Eight runs
   // of 4,096 to 32,768 particles, T = 1,454 to 4,000: 44 ms in one lane, 32 in
   // four; 32 runs of 774,144 particles: 399 and 319 ms.
@@ -1594,14 +1594,17 @@ smc_status smc_run_batch(int32_t n, const smc_model *const *models, smc_particle
       if (g > 0 && (st = lane_stream(g, &lanes[g].ls))) return st;
     }
   }
-  struct Join {
-    hipStream_t s;
-    std::vector<Lane> &lanes;
-    ~Join() {
-      for (Lane &l : lanes)
-        if (l.ls.s != s) (void)stream_after(s, l.ls.s, l.ls.ev);
+  // With an error, waits for all of the batch's work: decisions on their way
+  // to the slots would otherwise land in those of a later call, on another
+  // stream perhaps.  (A replay, which may be captured, has none.)
+  struct Finish {
+    const std::vector<Lane> &lanes;
+    bool wait;
+    ~Finish() {
+      if (wait)
+        for (const Lane &l : lanes) (void)hipStreamSynchronize(l.ls.s);
     }
-  } join{s, lanes};
+  } finish{lanes, !replay};
   for (Lane &l : lanes)
     if (l.ls.s != s && !stream_after(l.ls.s, s, l.ls.ev))
       return set_error(SMC_E_DEVICE, "batch: ordering the streams failed");
@@ -1869,6 +1872,7 @@ smc_status smc_run_batch(int32_t n, const smc_model *const *models, smc_particle
   for (Lane &l : lanes)
     if (l.ls.s != s && !stream_after(s, l.ls.s, l.ls.ev))
       return set_error(SMC_E_DEVICE, "batch: ordering the streams failed");
+  finish.wait = false;  // every decision has been read
   for (int i = 0; i < n; ++i) {
     recs[i].L = run[i].l;
     recs[i].evals = run[i].evals;
