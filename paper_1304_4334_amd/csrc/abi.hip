@@ -8,11 +8,13 @@
 #include <string.h>
 
 #include <chrono>
+#include <new>
 #include <vector>
 
 #include "batch.h"
 #include "common.h"
 #include "launch.h"
+#include "lease.h"
 #include "smc.h"
 
 namespace smc {
@@ -146,24 +148,6 @@ DecisionSlot *decision_slot() {
   return buf;
 }
 
-// The same for the runs of a batch, kMaxBatch of them 64 bytes apart.
-DecisionSlot *batch_slot(int i) {
-  constexpr size_t kStride = 64;
-  thread_local char *buf = nullptr;
-  thread_local bool tried = false;
-  if (!tried) {
-    tried = true;
-    void *p = nullptr;
-    const unsigned flags = hipHostMallocCoherent | hipHostMallocMapped | hipHostMallocPortable;
-    if (hipHostMalloc(&p, kMaxBatch * kStride, flags) == hipSuccess) {
-      buf = static_cast<char *>(p);
-      for (int k = 0; k < kMaxBatch; ++k)
-        *reinterpret_cast<DecisionSlot *>(buf + k * kStride) = DecisionSlot{};
-    }
-  }
-  return buf ? reinterpret_cast<DecisionSlot *>(buf + i * kStride) : nullptr;
-}
-
 // An event (no timing) of the calling thread for the current device, marking
 // the completion of a copy back so the host can wait for it alone while
 // later work stays queued; kept for the life of the process.
@@ -180,25 +164,87 @@ smc_status readback_event(hipEvent_t *out) {
   return SMC_OK;
 }
 
-// Further streams of the calling thread for the current device, with an event
-// each: the lanes of an adaptive batch.  Kept for the life of the process.
+// What an adaptive batch needs of the host: slots for its runs' decisions
+// (kMaxBatch of them 64 bytes apart, page-locked as decision_slot) and further
+// streams, with an event each, for its lanes (the first lane has the caller's).
 constexpr int kMaxLanes = 4;
 struct LaneStream {
   hipStream_t s = nullptr;
   hipEvent_t ev = nullptr;
 };
-smc_status lane_stream(int i, LaneStream *out) {
-  thread_local LaneStream lanes[16][kMaxLanes];
+struct BatchHost {
   int dev = -1;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 16)
-    return set_error(SMC_E_DEVICE, "batch lanes: device %d not supported", dev);
-  LaneStream &x = lanes[dev][i];
-  if ((!x.s && hipStreamCreateWithFlags(&x.s, hipStreamNonBlocking) != hipSuccess) ||
-      (!x.ev && hipEventCreateWithFlags(&x.ev, hipEventDisableTiming) != hipSuccess))
-    return set_error(SMC_E_DEVICE, "creating a batch lane failed");
-  *out = x;
-  return SMC_OK;
-}
+  uint32_t seq = 0;  // of the last decision asked for through these slots
+  char *slots = nullptr;
+  LaneStream lanes[kMaxLanes];
+
+  DecisionSlot *slot(int i) { return reinterpret_cast<DecisionSlot *>(slots + i * kSlotStride); }
+  smc_status init(int device) {
+    dev = device;
+    void *p = nullptr;
+    const unsigned flags = hipHostMallocCoherent | hipHostMallocMapped | hipHostMallocPortable;
+    if (hipHostMalloc(&p, kMaxBatch * kSlotStride, flags) != hipSuccess)
+      return set_error(SMC_E_DEVICE, "page-locked slots for the batch failed");
+    slots = static_cast<char *>(p);
+    for (int i = 0; i < kMaxBatch; ++i) *slot(i) = DecisionSlot{};
+    return SMC_OK;
+  }
+  smc_status lane(int i, LaneStream *out) {
+    LaneStream &x = lanes[i];
+    if ((!x.s && hipStreamCreateWithFlags(&x.s, hipStreamNonBlocking) != hipSuccess) ||
+        (!x.ev && hipEventCreateWithFlags(&x.ev, hipEventDisableTiming) != hipSuccess))
+      return set_error(SMC_E_DEVICE, "creating a batch lane failed");
+    *out = x;
+    return SMC_OK;
+  }
+  ~BatchHost() {
+    for (LaneStream &x : lanes) {
+      if (x.s) {
+        (void)hipStreamSynchronize(x.s);
+        (void)hipStreamDestroy(x.s);
+      }
+      if (x.ev) (void)hipEventDestroy(x.ev);
+    }
+    if (slots) (void)hipHostFree(slots);
+  }
+
+ private:
+  static constexpr size_t kSlotStride = 64;
+};
+
+// Lent to one batch call at a time; the store keeps up to four idle ones, so
+// that a program's next batch finds its streams made, for the life of the process
+// (it is not destroyed at exit, when the HIP runtime may be gone).
+class BatchLease {
+ public:
+  ~BatchLease() {
+    if (h_) delete store().give(h_);
+  }
+  smc_status take() {
+    int dev = -1;
+    if (hipGetDevice(&dev) != hipSuccess)
+      return set_error(SMC_E_DEVICE, "batch: no current device");
+    h_ = store().take([&](const BatchHost &x) { return x.dev == dev; });
+    if (h_) return SMC_OK;
+    h_ = new (std::nothrow) BatchHost;
+    if (!h_) return set_error(SMC_E_DEVICE, "batch: out of host memory");
+    const smc_status st = h_->init(dev);
+    if (st) {
+      delete h_;
+      h_ = nullptr;
+    }
+    return st;
+  }
+  BatchHost *operator->() { return h_; }
+
+ private:
+  static LeaseStore<BatchHost> &store() {
+    static auto *s = new LeaseStore<BatchHost>(4);
+    return *s;
+  }
+  BatchHost *h_ = nullptr;
+};
+
 // Work queued on `to` from now on waits for what `from` holds.
 bool stream_after(hipStream_t to, hipStream_t from, hipEvent_t ev) {
   return hipEventRecord(ev, from) == hipSuccess && hipStreamWaitEvent(to, ev, 0) == hipSuccess;
@@ -1555,9 +1601,8 @@ smc_status smc_run_batch(int32_t n, const smc_model *const *models, smc_particle
   // Every C-phase chunk's stopping decision is taken on the device and reaches
   // the host through the run's page-locked slot (a replay decides nothing, so
   // it can be captured).
-  if (!replay && !batch_slot(0))
-    return set_error(SMC_E_DEVICE, "page-locked slots for the batch failed");
-  thread_local uint32_t slot_seq = 0;
+  BatchLease host;
+  if (!replay && (st = host.take())) return st;
   // An adaptive batch runs in up to kMaxLanes lanes, each with a stream and a
   // part of the runs.  A lane's M iteration lasts as long as its longest run's,
   // and its C phases stand between its M iterations, so in one lane every run
@@ -1591,7 +1636,7 @@ smc_status smc_run_batch(int32_t n, const smc_model *const *models, smc_particle
       std::sort(lanes[g].runs.begin(), lanes[g].runs.end());
       lanes[g].queue = queue + 16 * g;
       lanes[g].ls.s = s;
-      if (g > 0 && (st = lane_stream(g, &lanes[g].ls))) return st;
+      if (g > 0 && (st = host->lane(g, &lanes[g].ls))) return st;
     }
   }
   // With an error, waits for all of the batch's work: decisions on their way
@@ -1704,14 +1749,14 @@ smc_status smc_run_batch(int32_t n, const smc_model *const *models, smc_particle
         StopInfo *stop_dev = ws_at<StopInfo>(pop, L.small + kSmallStop);
         int32_t *dflags = ws_at<int32_t>(pop, L.small + kSmallFlags);
         u.t1 = t1;
-        u.seq = ++slot_seq;
+        u.seq = ++host->seq;
         if ((st = launch_cscan(m->dev, P, pop->theta, pop->state, pop->logw, u.tc, t1, ce, u.t_stop,
                                u.zero_first, W, cs)) ||
             (st = launch_rss_scan(W, P, nc, rsscols, cs)) ||
             (st = launch_decide_commit(m->dev, P, pop->theta, pop->state, pop->logw, pop->loglik,
                                        u.zero_first,
                                        StopRule{rsscols, u.tc, t1, ce, u.t_stop, c.D1, stop_dev,
-                                                batch_slot(i), dflags, (int32_t)nc, u.seq},
+                                                host->slot(i), dflags, (int32_t)nc, u.seq},
                                        cs)) ||
             (st = launch_resample(pop->logw, pop->J, pop->N, c.scheme, c.rng.seed, c.rng.run,
                                   (uint64_t)(u.l + 1), pop->ancestor, ws_at<double>(pop, L.cum),
@@ -1838,7 +1883,7 @@ smc_status smc_run_batch(int32_t n, const smc_model *const *models, smc_particle
         const int i = pend[q];
         StopInfo got{};
         int32_t flags = 0;
-        if (!read_decision(batch_slot(i), run[i].seq, run[i].tc, run[i].t1, &got, &flags)) {
+        if (!read_decision(host->slot(i), run[i].seq, run[i].tc, run[i].t1, &got, &flags)) {
           ++q;
           continue;
         }
