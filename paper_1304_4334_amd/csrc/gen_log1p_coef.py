@@ -10,7 +10,7 @@ coefficients are rounded.  Run with `python gen_log1p_coef.py`; needs mpmath.
 import mpmath as mp
 
 mp.mp.dps = 50
-DEG = 7
+DEG = 6
 S = (mp.sqrt(2) - 1) / (mp.sqrt(2) + 1)
 HI = S * S
 
