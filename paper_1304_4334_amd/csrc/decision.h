@@ -25,7 +25,7 @@ struct StopInfo {
 // call's sequence number in one naturally aligned 8-byte word, so the host
 // never relies on a store wider than 8 bytes landing whole: it accepts the
 // slot only when all six pairs carry its sequence number.  The device writes
-// the 48 bytes as three 16-byte stores.
+// the 48 bytes as six 8-byte stores to system scope.
 //   payload 0, 1: t_commit (low, high); 2, 3: rss bits (low, high);
 //   4: flags; 5: bit 0 the phase ends, bit 1 the RSS fell below.
 struct alignas(16) DecisionSlot {

@@ -233,14 +233,21 @@ __global__ void __launch_bounds__(64) k_ccommit(DevModel dm, int64_t P, const do
       o.ends = first >= 0 || rule.t1 >= rule.t_max;
       *rule.out = o;
       if (rule.slot) {
-        const uint32_t seq = rule.seq;
+        // Stores to system scope: plain ones reached the host only with the end
+        // of the launch.  (First cycle of 16,000 egarch_23 FP64 particles, the
+        // decision in a launch of its own 85.2 us, here with plain stores
+        // 86.8, with these 83.0.)
         const int32_t fl = *rule.flags;
         const uint64_t tc = (uint64_t)o.t_commit;
         const uint64_t rb = __builtin_bit_cast(uint64_t, o.rss);
-        uint4 *dst = reinterpret_cast<uint4 *>(rule.slot);
-        dst[0] = make_uint4(seq, (uint32_t)tc, seq, (uint32_t)(tc >> 32));
-        dst[1] = make_uint4(seq, (uint32_t)rb, seq, (uint32_t)(rb >> 32));
-        dst[2] = make_uint4(seq, (uint32_t)fl, seq, (uint32_t)(o.ends | (o.below << 1)));
+        const uint32_t w[6] = {(uint32_t)tc, (uint32_t)(tc >> 32),
+                               (uint32_t)rb, (uint32_t)(rb >> 32),
+                               (uint32_t)fl, (uint32_t)(o.ends | (o.below << 1))};
+        uint64_t *dst = reinterpret_cast<uint64_t *>(rule.slot);
+#pragma unroll
+        for (int i = 0; i < 6; ++i)
+          __hip_atomic_store(dst + i, (uint64_t)w[i] << 32 | rule.seq, __ATOMIC_RELAXED,
+                             __HIP_MEMORY_SCOPE_SYSTEM);
       }
     }
   }
