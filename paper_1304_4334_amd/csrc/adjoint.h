@@ -161,17 +161,10 @@ struct Adjoint<Egarch<K, SH, R, I>> {
     z = fma(yv, p.isig, -p.mus);
     if constexpr (kT) {
       const R e = z * E;
-      const R h = (R)p.hnu1;
       const R q1 = fma(e * e, p.inu2, (R)1);
-      if constexpr (sizeof(R) == 4) {
-        eb = -h * (R)2 * e * p.inu2 / q1;
-        x[0] = e * e / q1;
-        x[1] = __builtin_amdgcn_logf(q1);
-      } else {
-        const R inv = (R)1 / q1;
-        eb = -h * (R)2 * p.inu2 * e * inv;
-        x[0] = e * e * inv;
-      }
+      eb = -(R)p.hnu1 * (R)2 * e * p.inu2 / q1;
+      x[0] = e * e / q1;
+      if constexpr (sizeof(R) == 4) x[1] = __builtin_amdgcn_logf(q1);
     } else if constexpr (kMix) {
       R dm[kNM], xi[kNM];
 #pragma unroll
