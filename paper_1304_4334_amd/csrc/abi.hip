@@ -129,10 +129,10 @@ int32_t state_bytes(const smc_model *m) { return m->dev.prec == SMC_FP32 ? 4 : 8
 
 // Page-locked, coherent host slot where the C-phase commit kernel stores
 // each chunk's decision and the numerical flags word (one per host thread,
-// kept for the life of the process); NULL if it cannot be had.  Device
-// stores to coherent host memory bypass the device caches, so the host needs
-// neither a fence nor an event: it watches the slot until every word carries
-// the call's sequence number while the work queued after the kernel runs on.
+// kept for the life of the process); NULL if it cannot be had.  The kernel's
+// stores go to system scope, so the host needs neither a fence nor an event: it
+// watches the slot until every word carries the call's sequence number while the
+// work queued after the kernel runs on.
 DecisionSlot *decision_slot() {
   thread_local DecisionSlot *buf = nullptr;
   thread_local bool tried = false;

@@ -267,7 +267,7 @@ smc_status launch_test_fns(const DevModel &m, int64_t P, const double *theta, co
 // with a heavy density, up to the population that fills the chip's SIMDs that
 // way.  Likelihoods over 1,000 observations, blocks at 32,768 vectors against
 // single waves at 32,832 (us): egarch_23 FP64 150 / 209, FP32 54 / 72,
-// egarch_12 FP64 112 / 162, EGARCH(2)-t FP64 89 / 90 (77 at 4,096); with
+// egarch_12 FP64 112 / 162, EGARCH(2)-t FP64 81 / 85 (76 at 4,096); with
 // 65,536 vectors single waves fill the SIMDs themselves.
 constexpr int64_t kSplitMaxP = 32768;
 inline bool split_density(const DevModel &m, int64_t P) {

@@ -798,7 +798,7 @@ __device__ __forceinline__ double ll_and_grad_block(const typename M::Y *__restr
 // turns while single waves still fill idle SIMDs.  Measured over 1,000
 // observations (blocks / single waves, us): EGARCH(2)-t FP32 111 / 250 at
 // 16,384, 208 / 253 at 32,768, and 250 for single waves up to 65,536; FP64 205
-// / 355 at 16,384 but 382 / 357 at 32,768; egarch_23 FP32 239 / 292 and FP64
+// / 367 at 16,384 but 405 / 377 at 32,768; egarch_23 FP32 239 / 292 and FP64
 // 549 / 496 at 32,768.
 template <class M>
 constexpr int64_t kGradBlockMaxP = sizeof(typename M::R) == 4 ? 32768 : 16384;
