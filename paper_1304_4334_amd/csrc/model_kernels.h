@@ -192,7 +192,8 @@ __global__ void __launch_bounds__(64) k_cscan(DevModel dm, int64_t P, const doub
 }
 
 // The first checked date of rule's chunk whose RSS is below rss_min, by a
-// whole wave: its column, or -1.  Eight loads of a lane are in flight.
+// whole wave: its column, or -1.  (The compiler loads a lane's eight values one
+// by one, as the ballots need them; most chunks are decided by the first.)
 __device__ __forceinline__ int decide_stop(const StopRule &rule) {
   for (int base = 0; base < rule.nc; base += 512) {
     double x[8];
